@@ -125,7 +125,7 @@ typedef struct mapl_codec_desc {
  *   L  > 0: for l = 0..L-1, codes[t,l] = argmin_j ||R_l[t] - C[l,j]||^2 with
  *           R_0 = Z0, R_{l+1} = R_l - C[l, codes[t,l]]; payload = codes [T,L]
  *           of code_dtype.  Distances are decided in fp32 from Z0 computed
- *           with fp32 accumulation (bf16 matrix-unit screening, then exact
+ *           with fp32 accumulation (16-bit matrix-unit screening, then exact
  *           fp32 rescoring of every codeword that could be nearest).
  *           group_dim 2: the same per group of two coordinates, codes
  *           [T, L, r/2] u8, exact fp32 distances.

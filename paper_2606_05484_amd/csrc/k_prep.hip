@@ -3,7 +3,7 @@
 //                   layouts the matrix units need (U~ [d,r] and U~^T [r,d])
 //   transpose_into  scaled transposed copies (anchor companions into the
 //                   concatenated weight operands)
-//   prep_codebook   bf16 screening copy of the codebooks plus fp32 norms
+//   prep_codebook   fp16 screening copy of the codebooks plus fp32 norms
 //   assemble        [Zhat | a_r] rows for the lift: Zhat is the payload or
 //                   the RVQ gather-sum sum_l C_l[code_l] (Sec. 3.5), a_r the
 //                   receiver's anchor row (Eq. 2)
@@ -58,36 +58,67 @@ __device__ __forceinline__ void transpose_tile(int bx, int by, const void* __res
   }
 }
 
-// One wave per (stage, codeword slot of a 64-codeword chunk): the bf16 copy
+// The power of two that takes a round's codebook into the screen's units:
+// the largest of a sample of its coordinates (four columns, other ones for
+// each codeword, of up to 1024 codewords) lands in [2^5, 2^6).  fp16 then
+// keeps 11 bits of every coordinate from 2^-19 of that up to 2^10 times it.
+// Every block computes the same value from the same sample (16 KB, read
+// while the block's rows are on their way); a poor sample costs speed only,
+// because the margins use the rounding errors that really occurred.
+__device__ __forceinline__ float rvq_round_scale(const float* __restrict__ C, int K, int r, float* red) {
+  const int n = min(K, 1024), q4 = r / 4;
+  const int64_t stride = K / n;
+  float m = 0.f;
+#pragma unroll 4
+  for (int i = threadIdx.x; i < n; i += 256) {
+    const float4 v = *(const float4*)(C + (int64_t)i * stride * r + 4 * ((i * 17) % q4));
+    m = fmaxf(m, fmaxf(fmaxf(fabsf(v.x), fabsf(v.y)), fmaxf(fabsf(v.z), fabsf(v.w))));
+  }
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) m = fmaxf(m, __shfl_xor(m, o, WAVE));
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = m;
+  __syncthreads();
+  m = fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3]));
+  if (!(m > 0.f)) return 1.f;
+  // exponent field e of m: 2^(5 - (e - 127)), kept a normal number
+  const int e = (int)(__float_as_uint(m) >> 23);
+  return __uint_as_float((uint32_t)min(max(127 + 5 + 127 - e, 1), 254) << 23);
+}
+
+// One wave per (stage, codeword slot of a 64-codeword chunk): the fp16 copy
 // with the norm columns of the RVQ screen appended (rows of r + 16), and the
-// fp32 squared norm, laid out per chunk as 64 consecutive floats.  A squared
-// norm x is stored as hi = bf16(x), mid = bf16(x - hi), lo = bf16(x - hi -
-// mid); each difference is exact in fp32 and an fp32 value has 24
-// significant bits, so hi + mid + lo = x exactly, in any order of addition.
+// fp32 squared norm, laid out per chunk as 64 consecutive floats, all in the
+// round's scaled units.  A squared norm x is stored as hi = bf16(x), mid =
+// bf16(x - hi), lo = bf16(x - hi - mid); each difference is exact in fp32 and
+// an fp32 value has 24 significant bits, so hi + mid + lo = x exactly, in any
+// order of addition.  A block's four slots are of one stage (a stage has a
+// multiple of 64).
 __device__ __forceinline__ void prep_codebook_block(int bx, const float* __restrict__ C, int L, int K, int r,
-                                                    bf16_t* __restrict__ Cb, float* __restrict__ meta) {
+                                                    bf16_t* __restrict__ Cb, float* __restrict__ meta,
+                                                    float* __restrict__ scales) {
+  __shared__ float red[4];
   const int nch = (K + 63) / 64;
   const int w = bx * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
-  if (w >= L * nch * 64) return;
-  const int l = w / (nch * 64), slot = w % (nch * 64);
+  const int l = min(w / (nch * 64), L - 1), slot = w % (nch * 64);
   const int j = slot;  // codeword index within stage l
   const int cols = rvq_cb_cols(r);
+  const float scale = rvq_round_scale(C + (int64_t)l * K * r, K, r, red);
   float s = 0.f, es = 0.f;
   if (j < K) {
     const float* row = C + ((int64_t)l * K + j) * r;
     for (int c = lane; c < r; c += 64) {
-      const float v = row[c];
+      const float v = row[c] * scale;
       s += v * v;
-      const uint32_t vb = f2bf(v);
-      const float d = v - bf2f(vb);  // the rounding error, exact in fp32
+      const uint32_t vb = pack_h2(fminf(fmaxf(v, -65504.f), 65504.f), 0.f) & 0xFFFFu;
+      const float d = v - h2f(vb);  // the rounding (or saturation) error
       es += d * d;
       Cb[((int64_t)l * K + j) * cols + c] = (bf16_t)vb;
     }
   }
   s = wave_sum(s);
   es = wave_sum(es);
-  // ||C_j - bf16(C_j)|| rounded up: es carries at most r ulps of accumulation error
-  const float eu = sqrtf(es) * (1.0f + 1.0f / 32768.0f);
+  // ||C_j - fp16(C_j)|| rounded up: es carries at most r ulps of accumulation error
+  const float eu = sqrtf(es) * (1.0f + 1.0f / 32768.0f) + rvq_flush(r);
   if (j < K && lane < 16) {
     // columns r .. r+2: the reduced norm n' = s - 1.01 k2 s in three pieces
     // (each difference exact in fp32, so they sum to n' exactly); columns
@@ -117,7 +148,8 @@ __device__ __forceinline__ void prep_codebook_block(int bx, const float* __restr
   if (lane == 0) {
     const int64_t m = ((int64_t)l * nch + j / 64) * 64 + (j % 64);
     meta[m] = s;
-    meta[(int64_t)L * nch * 64 + m] = eu;
+    meta[(int64_t)L * nch * 64 + m] = j < K ? eu : 0.f;
+    if (j == 0) scales[l] = scale;
   }
 }
 
@@ -293,8 +325,8 @@ __global__ void k_transpose_into(const void* __restrict__ src, int src_f32, int 
   transpose_tile(blockIdx.x, blockIdx.y, src, src_f32, rows, cols, lds, scale, dst, ldd, off);
 }
 __global__ void k_prep_codebook(const float* __restrict__ C, int L, int K, int r, bf16_t* __restrict__ Cb,
-                                float* __restrict__ meta) {
-  prep_codebook_block(blockIdx.x, C, L, K, r, Cb, meta);
+                                float* __restrict__ meta, float* __restrict__ scale) {
+  prep_codebook_block(blockIdx.x, C, L, K, r, Cb, meta, scale);
 }
 __global__ void k_assemble(AssembleArgs a) { assemble_block(blockIdx.x, a); }
 __global__ void k_gather_rows_bf16(const bf16_t* __restrict__ A, int k, const int32_t* __restrict__ ids, int V,
@@ -379,7 +411,7 @@ __global__ __launch_bounds__(256) void k_prep_batch(PrepBatch batch) {
     case PJ_TRANSPOSE:
       transpose_tile(b % j.gx, b / j.gx, j.src, j.src_f32, j.rows, j.cols, j.lds, j.scale, j.dst, j.ldd, j.off);
       break;
-    case PJ_CODEBOOK: prep_codebook_block(b, j.C, j.L, j.K, j.r, j.Cb, j.meta); break;
+    case PJ_CODEBOOK: prep_codebook_block(b, j.C, j.L, j.K, j.r, j.Cb, j.meta, j.cscale); break;
     case PJ_ASSEMBLE: assemble_block(b, j.asm_args); break;
     case PJ_ASSEMBLE_SUM: assemble_sum_block(b, j.asm_args); break;
     case PJ_GATHER: gather_rows_block(b, j.A, j.k, j.ids, j.V, j.T, j.out); break;
@@ -418,10 +450,12 @@ hipError_t launch_transpose_into(const void* src, int src_f32, int rows, int col
   return hipGetLastError();
 }
 
-hipError_t launch_prep_codebook(const float* C, int L, int K, int r, bf16_t* Cb, float* meta, hipStream_t s) {
+hipError_t launch_prep_codebook(const float* C, int L, int K, int r, bf16_t* Cb, float* meta, float* scale,
+                                hipStream_t s) {
   const int64_t slots = (int64_t)L * ((K + 63) / 64) * 64;
   if (slots <= 0) return hipSuccess;
-  hipLaunchKernelGGL(k_prep_codebook, dim3((unsigned)((slots + 3) / 4)), dim3(256), 0, s, C, L, K, r, Cb, meta);
+  hipLaunchKernelGGL(k_prep_codebook, dim3((unsigned)((slots + 3) / 4)), dim3(256), 0, s, C, L, K, r, Cb, meta,
+                     scale);
   return hipGetLastError();
 }
 
@@ -463,10 +497,10 @@ PrepJob prep_job_transpose(const void* src, int src_f32, int rows, int cols, int
   return j;
 }
 
-PrepJob prep_job_codebook(const float* C, int L, int K, int r, bf16_t* Cb, float* meta) {
+PrepJob prep_job_codebook(const float* C, int L, int K, int r, bf16_t* Cb, float* meta, float* scale) {
   PrepJob j{};
   j.kind = PJ_CODEBOOK;
-  j.C = C; j.L = L; j.K = K; j.r = r; j.Cb = Cb; j.meta = meta;
+  j.C = C; j.L = L; j.K = K; j.r = r; j.Cb = Cb; j.meta = meta; j.cscale = scale;
   j.blocks = (int)(((int64_t)L * ((K + 63) / 64) * 64 + 3) / 4);
   return j;
 }

@@ -3,29 +3,38 @@
 // current residual R_l and subtracts it.  Ties go to the lowest index.
 //
 // Decision procedure (exact with respect to the fp32 residual):
-//   screen  on the bf16 matrix units with R~ = bf16(R), C~ = bf16(C), the
-//           first k-step of every tile multiplying the codeword's norm
-//           columns by the token's norm operand, so the accumulator ends at
-//           a certified lower bound of the exact score s_j = ||C_j||^2 -
-//           2 R.C_j:  L_j = s~_j - Delta'_j,  s~_j = ||C_j||^2 - 2 R~.C~_j,
-//           where Delta'_j >= Delta_j bounds |s~_j - s_j| from the actual
-//           bf16 rounding-error norms of the token's residual and of the
-//           codeword, fp32 accumulation and norms, and the index tag below
-//           (see rvq_margin_ka/k2 and the norm columns in common.hpp): the
+//   screen  on the 16-bit matrix units with R~ = fp16(R), C~ = fp16(C) in
+//           the round's scaled units (a power of two from the codebook; see
+//           prep_codebook_block), the first k-step of every tile
+//           multiplying the codeword's bf16 norm columns by the token's norm
+//           operand, so the accumulator ends at a certified lower bound of
+//           the exact score s_j = ||C_j||^2 - 2 R.C_j:  L_j = s~_j -
+//           Delta'_j,  s~_j = ||C_j||^2 - 2 R~.C~_j, where Delta'_j >=
+//           Delta_j bounds |s~_j - s_j| from the actual fp16 rounding-error
+//           norms of the token's residual and of the codeword, fp32
+//           accumulation and norms, and the index tag below (see
+//           rvq_margin_ka/k2 and the norm columns in common.hpp): the
 //           margin is each codeword's own, not the codebook's largest.
 //   tag     the low 4 mantissa bits of L_j hold its slot among the 16
 //           scores a lane sees per tile, so a plain float min / med3 also
-//           yields the position; the tile of the smallest is tracked per
-//           tile.
-//   pass 1  per lane: the two smallest keys.  The nearest codeword j*
+//           yields the position; the tiles of the two smallest are tracked
+//           per tile.
+//   pass 1  per lane: the three smallest keys.  The nearest codeword j*
 //           satisfies L_j* <= s_j* <= s_j1 <= U = L_j1 + (1 + 1.03) Delta_j1
 //           for the smallest key j1, so it is among {j : L_j <= U}: a
-//           single codeword when the token's second key exceeds U (final).
-//   pass 2  (only in a workgroup with a token not final) lists every
-//           codeword with L_j <= U of those tokens: their B operands are
-//           compacted into 32-token tiles in LDS, and each wave screens a
-//           quarter of the codeword tiles against them, codebook fragments
-//           read straight from the L2-resident screening copy.
+//           single codeword when the token's second key exceeds U (final),
+//           the first and second keys of the two lane halves where both
+//           third keys exceed U.
+//   pass 2  (only in a workgroup with a token whose third key does not)
+//           lists every codeword with L_j <= U of those tokens: their B
+//           operands are compacted into 32-token tiles in LDS, and each wave
+//           screens a quarter of the codeword tiles against them, codebook
+//           fragments read straight from the L2-resident screening copy.
+// At the 1B-model boundary (T = 32768, r = 256, K = 1024, codewords drawn
+// from the residuals, a decaying spectrum) the bf16 screen left 34 % of the
+// token-rounds open, every workgroup in pass 2 and some tokens to a rescan of
+// the whole codebook: 420-510 us per call.  With fp16 7 % are open and a
+// sixth of the workgroup-rounds list: 130 us.
 //   rescore the listed candidates exactly in fp32 as sum_c (R_c - C_jc)^2:
 //           per wave a batch of up to 8 open tokens, their residual rows
 //           staged in LDS, 8 (token, codeword) pairs per step with coalesced
@@ -35,13 +44,13 @@
 // LDS rows), so screening and rescoring see the same R.
 //
 // Layout: a workgroup of 4 waves owns 128 tokens, 32 per wave.  A wave keeps
-// its tokens' bf16(-2R) as the B operand of v_mfma_f32_32x32x16_bf16 in
+// its tokens' fp16(-2R) as the B operand of v_mfma_f32_32x32x16_f16 in
 // registers (tokens along N); 64-codeword chunks of C~ (with the norm
 // columns) stream through three LDS stages filled by buffer_load ... lds
 // (direct-to-LDS, one __shared__ array per stage) as the A operand
 // (codewords along M).
 // Each lane thus sees the scores of ONE token for 16 codewords per tile;
-// the fold of one tile into (m1, m2) overlaps the matrix products of the
+// the fold of one tile into (m1, m2, m3) overlaps the matrix products of the
 // next.  The two lane halves that share a token merge at the end of a pass.
 #include "tn_gemm.hpp"
 
@@ -81,6 +90,16 @@ __device__ __forceinline__ int load_code(const void* codes, int cb, int64_t idx)
 
 // Row of a 32-codeword tile held by accumulator slot e of a lane in `half`.
 __device__ __forceinline__ int rq_row(int e, int half) { return 8 * (e >> 2) + 4 * half + (e & 3); }
+
+// One product of the screen: the norm step's columns are bf16, the
+// coordinates fp16.
+template <bool NORM>
+__device__ __forceinline__ f32x16_t rq_mfma(const uint4& a, const uint4& b, f32x16_t c) {
+  if constexpr (NORM)
+    return mfma32x32x16(a, b, c);
+  else
+    return mfma32x32x16h(a, b, c);
+}
 
 // A score tagged in its low 4 mantissa bits with its slot among the lane's
 // 16 scores of a tile (inline constants, one operation): a plain float min /
@@ -160,9 +179,12 @@ __device__ __forceinline__ void rvq_rounds(const RvqArgs& a, bf16_t* s0, bf16_t*
   for (int l = 0; l < a.L; ++l) {
     auto issue = [&](int q, bf16_t* sc) { issue_l(l, q, sc); };
 
-    // bf16(-2 R_l) in B-fragment layout, ||R_l||^2 and ||R_l - bf16(R_l)||^2
-    // from the fp32 residual (-2 bf16(v) = bf16(-2 v), and v - bf16(v) is
-    // exact in fp32)
+    // In the round's scaled units (the residual times the codebook's power
+    // of two): fp16(-2 R_l) in B-fragment layout, ||R_l||^2 and the rounding
+    // error ||R_l - R~_l||^2 with -2 R~ = fp16(-2 R) (the difference is exact
+    // in fp32; a coordinate past fp16's range makes it infinite, see `hard`).
+    // Coordinates stay scaled in this block only: res keeps the fp32 residual.
+    const float scale = a.scale[l], m2s = -2.f * scale;
     uint4 rb[NK16];
     float rn2 = 0.f, er2 = 0.f;
 #pragma unroll
@@ -171,11 +193,11 @@ __device__ __forceinline__ void rvq_rounds(const RvqArgs& a, bf16_t* s0, bf16_t*
       uint32_t w[4];
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
-        w[e] = pack_bf2(-2.f * v[2 * e], -2.f * v[2 * e + 1]);
-        const float d0 = fmaf(0.5f, __uint_as_float(w[e] << 16), v[2 * e]);
-        const float d1 = fmaf(0.5f, __uint_as_float(w[e] & 0xFFFF0000u), v[2 * e + 1]);
-        rn2 = fmaf(v[2 * e], v[2 * e], rn2);
-        rn2 = fmaf(v[2 * e + 1], v[2 * e + 1], rn2);
+        const float x0 = m2s * v[2 * e], x1 = m2s * v[2 * e + 1];
+        w[e] = pack_h2(x0, x1);
+        const float d0 = x0 - h2f(w[e] & 0xFFFFu), d1 = x1 - h2f(w[e] >> 16);
+        rn2 = fmaf(x0, x0, rn2);
+        rn2 = fmaf(x1, x1, rn2);
         er2 = fmaf(d0, d0, er2);
         er2 = fmaf(d1, d1, er2);
       }
@@ -183,9 +205,10 @@ __device__ __forceinline__ void rvq_rounds(const RvqArgs& a, bf16_t* s0, bf16_t*
     }
     rn2 += __shfl_xor(rn2, 32, WAVE);
     er2 += __shfl_xor(er2, 32, WAVE);
-    // norms rounded up (each sum carries at most R ulps of accumulation error)
-    const float rnorm = sqrtf(rn2) * (1.0f + 1.0f / 32768.0f);
-    const float enorm = sqrtf(er2) * (1.0f + 1.0f / 32768.0f);
+    // norms of R, half those of -2 R, rounded up (each sum carries at most R
+    // ulps of accumulation error)
+    const float rnorm = 0.5f * sqrtf(rn2) * (1.0f + 1.0f / 32768.0f);
+    const float enorm = 0.5f * sqrtf(er2) * (1.0f + 1.0f / 32768.0f) + rvq_flush(R);
     // the margin's coefficient of ||C_j|| (b) and of e_j (c)
     const float bco = 2.0f * enorm * 1.0078125f + rvq_margin_ka(R) * rnorm;
     const float cco = 2.0f * rnorm;
@@ -267,10 +290,8 @@ __device__ __forceinline__ void rvq_rounds(const RvqArgs& a, bf16_t* s0, bf16_t*
           constexpr int PI = decltype(pc)::value, CT = PI / P, S = PI % P;
           constexpr int AHEAD = (NP2 - 1 - PI) < (W - 1) ? (NP2 - 1 - PI) : (W - 1);
           lds_wait_n<AHEAD>(fw[PI % W]);
-          if constexpr (CT == 0)
-            acc0 = mfma32x32x16(as_uint4(fw[PI % W]), opnd(std::integral_constant<int, S>{}), acc0);
-          else
-            acc1 = mfma32x32x16(as_uint4(fw[PI % W]), opnd(std::integral_constant<int, S>{}), acc1);
+          f32x16_t& acc = CT == 0 ? acc0 : acc1;
+          acc = rq_mfma<S == 0>(as_uint4(fw[PI % W]), opnd(std::integral_constant<int, S>{}), acc);
           __builtin_amdgcn_sched_barrier(0);
           if constexpr (PI + W < NP2) read(std::integral_constant<int, PI + W>{});
           constexpr int E0 = S * FPS < 16 ? S * FPS : 16, E1 = (S + 1) * FPS < 16 ? (S + 1) * FPS : 16;
@@ -309,11 +330,12 @@ __device__ __forceinline__ void rvq_rounds(const RvqArgs& a, bf16_t* s0, bf16_t*
     // (the screen subtracts that codeword's own error bound), and s_j1 <= U =
     // L_j1 + (RVQ_SUB_FACTOR + 1) Delta_j1 for the smallest key j1 (of equal
     // keys, half 0's), so only codewords with L_j <= U can be nearest.
-    //  pass 1: per lane the two smallest keys and the position of the
-    //    first; a token is final when its second key exceeds U;
-    //  pass 2 (only in a workgroup with an open token): every key <= U of
-    //    the open tokens listed (the open tokens compacted); the candidates
-    //    are rescored exactly in fp32.
+    //  pass 1: per lane the three smallest keys and the positions of the first
+    //    two; a token is final when its second key exceeds U; its listed keys
+    //    are all its candidates when the third keys of both halves exceed U;
+    //  pass 2 (only in a workgroup with a token whose third key does not):
+    //    every key <= U of those tokens listed (the tokens compacted); the
+    //    candidates are rescored exactly in fp32.
     const float* n2l = a.meta + (int64_t)l * nchunks * 64;
     const float* e2l = n2l + (int64_t)a.L * nchunks * 64;
     auto margin = [&](int j) {  // Delta_j, rounded up
@@ -322,42 +344,66 @@ __device__ __forceinline__ void rvq_rounds(const RvqArgs& a, bf16_t* s0, bf16_t*
       return (cco * e2l[jj] + bco * (sqrtf(n2) * (1.0f + 1.0f / 32768.0f)) + rvq_margin_k2(R) * n2) * 1.0002f +
              1e-30f;
     };
-    // ---- pass 1: the two smallest keys per lane (slot tags) and the tile
-    // of the smallest
+    // ---- pass 1: the three smallest keys per lane (slot tags) and the tiles
+    // of the first two
     int j1;
     float thr;
-    bool open;  // not final: the token's candidates are listed by pass 2
+    bool open, need2;  // not final; its candidates have to be listed by pass 2
     {
-      float m1 = INFINITY, m2 = INFINITY, m1_in = INFINITY;
-      int tile1 = 0;
-      pass([&]() { m1_in = m1; },
+      float m1 = INFINITY, m2 = INFINITY, m3 = INFINITY, m1_in = INFINITY, m2_in = INFINITY;
+      int tile1 = 0, tile2 = 0;
+      pass([&]() { m1_in = m1; m2_in = m2; },
            [&](const f32x16_t& acc, int, auto ec) {
              constexpr int E = decltype(ec)::value;
              const float key = rq_tag_slot(acc[E], E);
+             m3 = __builtin_amdgcn_fmed3f(m2, m3, key);
              m2 = __builtin_amdgcn_fmed3f(m1, m2, key);
              m1 = __builtin_amdgcn_fmed3f(m1, key, -3.40282347e38f);  // min for finite keys
            },
-           [&](int tile) { tile1 = m1 < m1_in ? tile : tile1; }, true);
-      const float o1 = __shfl_xor(m1, 32, WAVE), o2 = __shfl_xor(m2, 32, WAVE);
+           [&](int tile) {
+             // a new smallest key displaces the old one to second place or
+             // has a second of its own tile beside it (where both are equal,
+             // so is the third, and the token is not decided from keys)
+             const bool n1 = m1 < m1_in;
+             tile2 = n1 ? (m2 == m1_in ? tile1 : tile) : (m2 < m2_in ? tile : tile2);
+             tile1 = n1 ? tile : tile1;
+           },
+           true);
+      const float o1 = __shfl_xor(m1, 32, WAVE), o2 = __shfl_xor(m2, 32, WAVE), o3 = __shfl_xor(m3, 32, WAVE);
       const int own_j1 = tile1 * 32 + rq_row((int)(__float_as_uint(m1) & 15u), half);
+      const int own_j2 = tile2 * 32 + rq_row((int)(__float_as_uint(m2) & 15u), half);
       const int o_j1 = __shfl_xor(own_j1, 32, WAVE);
       j1 = (m1 < o1 || (m1 == o1 && half == 0)) ? own_j1 : o_j1;
       const float k2 = fminf(fmaxf(m1, o1), fminf(m2, o2));
       thr = fminf(m1, o1) + (RVQ_SUB_FACTOR + 1.0f) * margin(j1);
-      open = valid && !(k2 > thr);
-      if (half == 0) cand_cnt[tl] = 0;
+      // hard: a residual or a codeword far out of the screen's range (the
+      // bounds are not finite): every codeword is a candidate.  A NaN residual
+      // has no nearest codeword and takes 0.
+      const bool nan = rn2 != rn2;
+      const bool hard = !(rn2 < 1e30f) || !(fabsf(thr) < 1e37f);
+      open = valid && !nan && (hard || !(k2 > thr));
+      j1 = nan ? 0 : j1;
+      // a token whose third keys exceed U is rescored from its listed first
+      // and second keys; only another one needs the listing pass
+      need2 = open && !hard && !(fminf(m3, o3) > thr);
+      const int n_own = (m1 <= thr ? 1 : 0) + (m2 <= thr ? 1 : 0);
+      const int n_o = (o1 <= thr ? 1 : 0) + (o2 <= thr ? 1 : 0);
+      if (half == 0) cand_cnt[tl] = need2 ? 0 : hard ? RQ_CAP + 1 : n_own + n_o;
+      const int at = half == 0 ? 0 : n_o;
+      if (n_own > 0) cand[tl][at] = (uint16_t)own_j1;
+      if (n_own > 1) cand[tl][at + 1] = (uint16_t)own_j2;
     }
-    const int any_open = __syncthreads_or(open ? 1 : 0);
+    const int any_need2 = __syncthreads_or(need2 ? 1 : 0);
     if (a.stats && tid == 0) {
       atomicAdd(&a.stats[4], 1);
-      if (any_open) atomicAdd(&a.stats[3], 1);
+      if (any_need2) atomicAdd(&a.stats[3], 1);
     }
 
     int jstar = j1;
-    if (any_open) {
+    if (any_need2) {
       // ---- pass 2: list every key <= U of the open tokens.  The open
       // tokens are compacted: each writes its MFMA B operand (the 17 k-steps
-      // of bf16(-2R) and the norm operand, 16 B per lane half and k-step) to
+      // of fp16(-2R) and the norm operand, 16 B per lane half and k-step) to
       // a row of stages 0 and 1 (free until the next round's loads), its
       // threshold and index to a table; then every wave takes 32 compacted
       // tokens at a time against its quarter of the codeword tiles, the
@@ -370,13 +416,13 @@ __device__ __forceinline__ void rvq_rounds(const RvqArgs& a, bf16_t* s0, bf16_t*
         return c < CAP0 ? (char*)s0 + (int64_t)c * TB : (char*)s1 + (int64_t)(c - CAP0) * TB;
       };
       {
-        const uint64_t ob = __ballot(half == 0 && open);
+        const uint64_t ob = __ballot(half == 0 && need2);
         if (lane == 0) sm.wcnt[wave] = __popcll(ob);
         __syncthreads();
         int base = 0;
 #pragma unroll
         for (int w = 0; w < 4; ++w) base += w < wave ? sm.wcnt[w] : 0;
-        if (open) {
+        if (need2) {
           const int c = base + __popcll(ob & ((1ull << (lane & 31)) - 1ull));
           char* rw = crow(c) + 16 * half;
 #pragma unroll
@@ -434,7 +480,7 @@ __device__ __forceinline__ void rvq_rounds(const RvqArgs& a, bf16_t* s0, bf16_t*
           }
           f32x16_t acc = f32x16_t{};
 #pragma unroll
-          for (int p = 0; p <= NK16; ++p) acc = mfma32x32x16(af[p], bq[p], acc);
+          for (int p = 0; p <= NK16; ++p) acc = p == 0 ? rq_mfma<true>(af[p], bq[p], acc) : rq_mfma<false>(af[p], bq[p], acc);
           uint32_t hit = 0;
 #pragma unroll
           for (int e = 0; e < 16; ++e) hit |= acc[e] <= cthr ? (1u << e) : 0u;
@@ -446,6 +492,8 @@ __device__ __forceinline__ void rvq_rounds(const RvqArgs& a, bf16_t* s0, bf16_t*
         }
       }
       __syncthreads();  // every list is complete, stages 0 and 1 are read
+    }
+    {
       // ---- exact fp32 rescoring of the open tokens, wave by wave (each wave
       // its own 32), a batch of up to 8 tokens at a time: their residuals go
       // to the wave's share of stage 2, their (token, codeword) pairs are

@@ -127,14 +127,17 @@ hipError_t launch_prep_u(const float* U, int d, int r, bf16_t* Ub, int64_t ldub,
 // or bf16 source.
 hipError_t launch_transpose_into(const void* src, int src_f32, int rows, int cols, int64_t lds,
                                  float scale, bf16_t* dst, int64_t ldd, int off, hipStream_t s);
-// Screening copy of the codebooks, rows of rvq_cb_cols(r) = r + 16 bf16:
-// Cb[l][j][0:r] = bf16(C[l][j]), Cb[l][j][r:r+3] = hi, mid, lo with
-// hi + mid + lo = ||C_j||^2 exactly (fp32 split into three bf16 pieces),
-// Cb[l][j][r+3:r+5] = ||C_j|| rounded up (two pieces), Cb[l][j][r+5] =
-// ||C_j - bf16(C_j)|| rounded up, Cb[l][j][r+6:r+16] = 0.  meta[0][l][chunk][64]:
-// ||C_j||^2 in fp32 per 64-codeword chunk, meta[1][l][chunk][64]:
-// ||C_j - bf16(C_j)|| rounded up (zero past K).
-hipError_t launch_prep_codebook(const float* C, int L, int K, int r, bf16_t* Cb, float* meta, hipStream_t s);
+// Screening copy of the codebooks in scaled units C' = scale[l] C (a power of
+// two per round), rows of rvq_cb_cols(r) = r + 16 16-bit columns:
+// Cb[l][j][0:r] = fp16(C'[l][j]) (saturated), then bf16 columns
+// Cb[l][j][r:r+3] = hi, mid, lo with hi + mid + lo = the reduced ||C'_j||^2
+// exactly (fp32 split into three bf16 pieces), Cb[l][j][r+3:r+5] = ||C'_j||
+// rounded up (two pieces), Cb[l][j][r+5] = ||C'_j - fp16(C'_j)|| rounded up,
+// Cb[l][j][r+6:r+16] = 0.  meta[0][l][chunk][64]: ||C'_j||^2 in fp32 per
+// 64-codeword chunk, meta[1][l][chunk][64]: ||C'_j - fp16(C'_j)|| rounded up
+// (zero past K).
+hipError_t launch_prep_codebook(const float* C, int L, int K, int r, bf16_t* Cb, float* meta, float* scale,
+                                hipStream_t s);
 inline int64_t rvq_meta_floats(int L, int K) { return 2 * (int64_t)L * ((K + 63) / 64) * 64; }
 __host__ __device__ constexpr int rvq_cb_cols(int r) { return r + 16; }
 
@@ -167,7 +170,7 @@ struct PrepJob {
   // PJ_TRANSPOSE, PJ_SMALL_GEMM (dst, ldd, off, scale)
   const void* src; int src_f32, rows, cols; int64_t lds; float scale; bf16_t* dst; int64_t ldd; int off;
   // PJ_CODEBOOK
-  const float* C; int L, K; bf16_t* Cb; float* meta;
+  const float* C; int L, K; bf16_t* Cb; float* meta; float* cscale;
   // PJ_ASSEMBLE, PJ_ASSEMBLE_SUM (codeword sums only: L <= 2, no anchor columns)
   AssembleArgs asm_args;
   // PJ_GATHER
@@ -185,20 +188,21 @@ struct PrepBatch {
 PrepJob prep_job_u(const float* U, int d, int r, bf16_t* Ub, int64_t ldub, bf16_t* Ut, int64_t ldut);
 PrepJob prep_job_transpose(const void* src, int src_f32, int rows, int cols, int64_t lds, float scale, bf16_t* dst,
                            int64_t ldd, int off);
-PrepJob prep_job_codebook(const float* C, int L, int K, int r, bf16_t* Cb, float* meta);
+PrepJob prep_job_codebook(const float* C, int L, int K, int r, bf16_t* Cb, float* meta, float* scale);
 PrepJob prep_job_assemble(const AssembleArgs& a);
 PrepJob prep_job_gather(const bf16_t* A, int k, const int32_t* ids, int V, int T, bf16_t* out);
 PrepJob prep_job_small_gemm(const bf16_t* P, int64_t ldp, const float* Q, int64_t ldq, int qt, int M, int N,
                             int Kd, float scale, bf16_t* dst, int64_t ldd, int off);
 hipError_t launch_prep_batch(const PrepJob* jobs, int n, hipStream_t s);
 
-// ---------------------------------------------------------------- RVQ (bf16 screen + fp32 rescore)
+// ---------------------------------------------------------------- RVQ (fp16 screen + fp32 rescore)
 // r in {32, 64, 128, 256}.
 struct RvqArgs {
   const float* Z0;     // [T,r] fp32 unquantised coordinates
-  const bf16_t* Cb;    // [L,K,r+16] bf16 screening copy with the split norms (rvq_cb_cols)
+  const bf16_t* Cb;    // [L,K,r+16] fp16 screening copy with the split norms (rvq_cb_cols)
   const float* C;      // [L,K,r] fp32 codebooks
-  const float* meta;   // [2][L][ceil(K/64)][64]: ||C_j||^2, ||C_j - bf16(C_j)|| (rvq_meta_floats)
+  const float* meta;   // [2][L][ceil(K/64)][64]: ||C'_j||^2, ||C'_j - fp16(C'_j)|| (rvq_meta_floats)
+  const float* scale;  // [L] the rounds' powers of two
   int T, r, L, K;
   void* codes; int code_bytes;  // [T,L]
   int* stats;          // [8] optional counters, may be null: tokens rescored, their candidates,

@@ -154,6 +154,8 @@ SplitPlan plan_splits(int64_t T, int Ma, int Mg, int N) {
   return {(int)splits, (int)tps};
 }
 
+constexpr int kStatsInts = 8;  // RVQ decision counters; the rounds' codebook scales follow them
+
 struct Layout {
   size_t total = 0;
   size_t w = 0, w2 = 0, z0 = 0, cb = 0, cn2 = 0, cnr = 0, stats = 0, flag = 0;
@@ -194,7 +196,7 @@ Layout layout(const mapl_codec_desc& D, int call, const GradQ* q = nullptr) {
           if (!enc_rvq_fusable((int)r, D.L)) Lo.z0 = c.take((size_t)T * r * 4);
           Lo.cb = c.take((size_t)D.L * D.K * rvq_cb_cols((int)r) * 2);
           Lo.cn2 = c.take((size_t)rvq_meta_floats(D.L, D.K) * 4);
-          Lo.stats = c.take(32);
+          Lo.stats = c.take((kStatsInts + 8) * 4);  // decision counters, codebook scales
         }
         break;
       case MAPL_CALL_DECODE:
@@ -211,7 +213,7 @@ Layout layout(const mapl_codec_desc& D, int call, const GradQ* q = nullptr) {
           if (!enc_rvq_fusable((int)r, q->L)) Lo.z0 = c.take((size_t)T * r * 4);
           Lo.cb = c.take((size_t)q->L * q->K * rvq_cb_cols((int)r) * 2);
           Lo.cn2 = c.take((size_t)rvq_meta_floats(q->L, q->K) * 4);
-          Lo.stats = c.take(32);
+          Lo.stats = c.take((kStatsInts + 8) * 4);  // decision counters, codebook scales
         }
         break;
       case MAPL_CALL_ENCODE_BWD: {
@@ -424,6 +426,7 @@ extern "C" int mapl_encode(const mapl_codec_desc* desc, const void* X, const int
     bf16_t* Wt = at<bf16_t>(ws, Lo.w);
     bf16_t* Cb = D.L > 0 ? at<bf16_t>(ws, Lo.cb) : nullptr;
     float* meta = D.L > 0 ? at<float>(ws, Lo.cn2) : nullptr;
+    float* cscale = D.L > 0 ? at<float>(ws, Lo.stats) + kStatsInts : nullptr;
     PrepJob jobs[3];
     int nj = 0;
     jobs[nj++] = prep_job_u(U, (int)d, (int)r, nullptr, 0, Wt, Lo.kw);
@@ -434,7 +437,7 @@ extern "C" int mapl_encode(const mapl_codec_desc* desc, const void* X, const int
       else
         jobs[nj++] = prep_job_transpose(B_s, 0, (int)k, (int)r, r, -1.f, Wt, Lo.kw, (int)d);
     }
-    if (D.L > 0 && !grouped(D)) jobs[nj++] = prep_job_codebook(C, D.L, D.K, (int)r, Cb, meta);
+    if (D.L > 0 && !grouped(D)) jobs[nj++] = prep_job_codebook(C, D.L, D.K, (int)r, Cb, meta, cscale);
     LAUNCH("enc:prep", launch_prep_batch(jobs, nj, s));
     TnArgs g{};
     g.A = (const bf16_t*)X; g.lda = d; g.Ka = (int)d;
@@ -454,7 +457,7 @@ extern "C" int mapl_encode(const mapl_codec_desc* desc, const void* X, const int
       return MAPL_OK;
     }
     RvqArgs a{};
-    a.Z0 = nullptr; a.Cb = Cb; a.C = C; a.meta = meta;
+    a.Z0 = nullptr; a.Cb = Cb; a.C = C; a.meta = meta; a.scale = cscale;
     a.T = (int)T; a.r = (int)r; a.L = D.L; a.K = D.K;
     a.codes = payload; a.code_bytes = cbytes;
     a.stats = nullptr;
@@ -683,7 +686,8 @@ int decode_bwd_impl(const mapl_codec_desc* desc, const void* dXhat, const void* 
     jobs[nj++] = prep_job_u(U, (int)d, (int)r, nullptr, 0, Ut, d);
     bf16_t* Cbq = q ? at<bf16_t>(ws, Lo.cb) : nullptr;
     float* metaq = q ? at<float>(ws, Lo.cn2) : nullptr;
-    if (q) jobs[nj++] = prep_job_codebook(q->C, q->L, q->K, (int)r, Cbq, metaq);
+    float* scaleq = q ? at<float>(ws, Lo.stats) + kStatsInts : nullptr;
+    if (q) jobs[nj++] = prep_job_codebook(q->C, q->L, q->K, (int)r, Cbq, metaq, scaleq);
     const bf16_t* Q = (const bf16_t*)payload;
     if (D.L > 0 || need_anchor) {
       bf16_t* Ah = at<bf16_t>(ws, Lo.ahat);
@@ -706,7 +710,7 @@ int decode_bwd_impl(const mapl_codec_desc* desc, const void* dXhat, const void* 
     } else {
       // the gradient's RVQ, as the encoder's: fused with the GEMM at r = 256
       RvqArgs a{};
-      a.Cb = Cbq; a.C = q->C; a.meta = metaq;
+      a.Cb = Cbq; a.C = q->C; a.meta = metaq; a.scale = scaleq;
       a.T = (int)T; a.r = (int)r; a.L = q->L; a.K = q->K;
       a.codes = q->codes; a.code_bytes = q->code_bytes;
       if (enc_rvq_fusable((int)r, q->L)) {

@@ -1,0 +1,121 @@
+"""The fp16 screen of the RVQ encoder at the edges of its range and of its
+candidate lists.
+
+The screen runs in units of a power of two per round (from a sample of the
+codebook's coordinates) and decides a token only where its certified bounds
+do; every code is still the exact fp32 argmin.  Checked here: the bound
+itself in float64 (CPU), and on the GPU codebooks of extreme scale, codewords
+and tokens far outside fp16's range, and near ties that fall on the two
+lane halves and their first, second and third keys."""
+import numpy as np
+import pytest
+
+from oracle import codec as ocodec
+from paper_2606_05484_amd import mapl, synth
+from _helpers import Dev, codes_np, compare_codes, descr, f64, run_encode, stress_codebooks
+
+SMALL = dict(T=300, d=512, r=64, V=300, k=16, L=2, K=64, dtype="bf16", alpha=0.8, n_out=4, cb_sigma=None, gscale=1.0)
+
+
+def _flush16(x):
+    """fp16 rounding, saturated, subnormals taken as zero (the worst a matrix unit may do)."""
+    y = np.clip(x, -65504.0, 65504.0).astype(np.float16).astype(np.float64)
+    return np.where(np.abs(y) < 2.0 ** -14, 0.0, y)
+
+
+@pytest.mark.parametrize("r", [64, 128, 256])
+@pytest.mark.parametrize("spread", [0.0, 3.0, 30.0])
+def test_margin_bounds_the_screen_error(r, spread):
+    """|s~_j - s_j| <= Delta_j with the kernel's formula, the kernel's error
+    norms taken with subnormals kept and the per-coordinate allowance added."""
+    rng = np.random.default_rng(r + int(spread))
+    mag = np.exp(-spread * rng.uniform(0, 1, (2, r)))  # coordinates over e^30 of magnitudes
+    R = 2.0 ** rng.uniform(-4, 9, (200, 1)) * mag[0] * rng.standard_normal((200, r))
+    C = 40.0 * mag[1] * rng.standard_normal((100, r))
+    C[0] *= 1e4  # saturates
+    C[1] = 0.0
+    Rq, Cq = _flush16(-2 * R) / -2, _flush16(C)
+    ka = (8 * r / 2 ** 24 + 2.0 ** -20 + 2.0 ** -16) * 1.0078125
+    k2 = 4 * (r + 4) / 2 ** 24 + 2.0 ** -17
+    flush = 2.0 ** -14 * np.sqrt(r)
+    eR = np.linalg.norm(R - (-2 * R).astype(np.float16).astype(np.float64) / -2, axis=1) + flush
+    with np.errstate(over="ignore"):
+        Ck = np.clip(C, -65504, 65504).astype(np.float16).astype(np.float64)
+    ej = np.linalg.norm(C - Ck, axis=1) + flush
+    nR, nC = np.linalg.norm(R, axis=1), np.linalg.norm(C, axis=1)
+    err = np.abs(2 * R @ C.T - 2 * Rq @ Cq.T)
+    delta = 2 * nR[:, None] * ej + 2 * eR[:, None] * (1 + 2.0 ** -8) * nC + ka * nR[:, None] * nC + k2 * nC ** 2
+    assert (err <= delta).all()
+
+
+def _encode(x, C):
+    D = descr(x)
+    print("encode", x["T"], x["r"], x["K"], flush=True)
+    return codes_np(run_encode(x, D, Dev(x, C)), D)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("r", [64, 128, 256])
+@pytest.mark.parametrize("q", [-60, 0, 40])
+def test_codebook_scale(r, q):
+    """Projector and codebooks times 2^q: the same codes at any scale (the
+    squared norms stay inside fp32)."""
+    x = synth.codec_inputs(None, seed=31, **dict(SMALL, r=r))
+    C = stress_codebooks(x, 7)
+    x["U"] = (x["U"] * np.float32(2.0 ** q)).astype(np.float32)
+    C = (C * np.float32(2.0 ** q)).astype(np.float32)
+    Z0 = ocodec.project(f64(x, "X"), x["ids"], x["U"], f64(x, "A"), f64(x, "B"), "ambient", "bf16")
+    ref, gap, _ = ocodec.rvq_encode(Z0, C)
+    bad, ex = compare_codes(_encode(x, C), ref, gap)
+    print("mismatched", bad, "exempt", ex)
+    assert bad == 0
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("r", [64, 128, 256])
+def test_out_of_range_token_and_codeword(r):
+    """A token 2^13 times the others and a codeword on it whose sampled
+    coordinates are zero, so the round's scale does not see it: the codeword
+    saturates, the token leaves fp16, and both are decided exactly."""
+    x = synth.codec_inputs(None, seed=32, **dict(SMALL, r=r, k=0))
+    C = stress_codebooks(x, 8)
+    X = x["X"].copy()
+    X[7] = np.where(X[7] & 0x7F80, X[7] + (13 << 7), X[7])  # bf16 bits: the exponent up by 13
+    x["X"] = X
+    Z0 = ocodec.project(f64(x, "X"), x["ids"], x["U"], f64(x, "A"), f64(x, "B"), "ambient", "bf16")
+    C[0, 5] = Z0[7]
+    c0 = 4 * ((5 * 17) % (r // 4))
+    C[0, 5, c0:c0 + 4] = 0.0
+    ref, gap, _ = ocodec.rvq_encode(Z0, C)
+    assert ref[7, 0] == 5 and gap[7, 0] > 1e-2
+    got = _encode(x, C)
+    bad, ex = compare_codes(got, ref, gap)
+    print("mismatched", bad, "exempt", ex, "token 7", got[7], ref[7])
+    assert got[7, 0] == 5 and bad == 0
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("r", [64, 128, 256])
+@pytest.mark.parametrize("rows", [(0, 1), (0, 4), (0, 1, 2), (3, 8, 40), (0, 1, 4, 5), (0, 1, 4, 5, 8, 12),
+                                  tuple(range(40, 60))])
+def test_near_ties_by_lane_half(r, rows):
+    """Codewords at squared distances (1e-3 + 4e-5 i) ||Z0||^2 around one
+    token, the nearest at the last of the given rows.  Rows 0-3, 8-11, ... of
+    a 32-row tile belong to one lane half, 4-7, 12-15, ... to the other: up
+    to two per half are decided from the kept keys, more by the listing pass,
+    and twenty overflow the list."""
+    x = synth.codec_inputs(None, seed=33, **dict(SMALL, r=r, k=16))
+    Z0 = ocodec.project(f64(x, "X"), x["ids"], x["U"], f64(x, "A"), f64(x, "B"), "ambient", "bf16")
+    rng = np.random.default_rng(3)
+    sig = float(np.sqrt(np.mean(Z0 ** 2)))
+    C = (sig * (5 + rng.standard_normal((2, 64, r)))).astype(np.float32)
+    z, n2 = Z0[5], float(Z0[5] @ Z0[5])
+    for i, j in enumerate(reversed(rows)):
+        u = rng.standard_normal(r)
+        C[0, j] = (z + np.sqrt((1e-3 + 4e-5 * i) * n2) * u / np.linalg.norm(u)).astype(np.float32)
+    ref, gap, _ = ocodec.rvq_encode(Z0, C)
+    assert ref[5, 0] == rows[-1] and gap[5, 0] > 2e-5  # fp32 distances resolve 1e-6 ||Z0||^2 here
+    got = _encode(x, C)
+    bad, ex = compare_codes(got, ref, gap)
+    print("token 5", got[5], "mismatched", bad, "exempt", ex)
+    assert got[5, 0] == rows[-1] and bad == 0
