@@ -1,11 +1,10 @@
-// Batched strided GEMM with fp32 results:
+// Batched strided fp32 GEMM:
 //   C[b](m,n) = alpha_b * sum_k A[b](m,k) B[b](k,n) + beta_b * Cin[b](m,n)
 // with alpha_b = alpha * (alpha_ptr ? alpha_ptr[b] : 1), likewise beta, on
-// the fp32 matrix units (v_mfma_f32_32x32x2_f32) or, for fp32 operands with
-// GEMM_SPLIT_F16, as products of fp16 pieces on the 16-bit matrix units
-// (k_gemm_x3).  Operands may be fp32 or bf16 (widened exactly to fp32 in
-// LDS); any element strides, so transposed operands need no copies.  These
-// kernels carry every product of the Stiefel step and the fp32 codec path.
+// the fp32 matrix units (v_mfma_f32_32x32x2_f32) or, with GEMM_SPLIT_F16, as
+// products of fp16 pieces on the 16-bit matrix units (k_gemm_x3).  Products
+// with few output tiles, or with strides that the vector loads here do not
+// take, run in k_gemm_f32s.hip.
 #include "common.hpp"
 #include "kernels.hpp"
 
@@ -13,105 +12,11 @@ namespace mapl {
 
 namespace {
 
-constexpr int GF_BM = 128, GF_BN = 128, GF_BK = 16, GF_PAD = 1;
 constexpr int GF_THREADS = 256;
 
-template <typename T>
-__device__ __forceinline__ float ld_elem(const T* p);
-template <>
-__device__ __forceinline__ float ld_elem<float>(const float* p) { return *p; }
-template <>
-__device__ __forceinline__ float ld_elem<bf16_t>(const bf16_t* p) { return bf2f(*p); }
-
-// Load a [BM x BK] tile of op(A) (element (m,k) at A + m*sm + k*sk) into
-// LDS as s[k][m].  Consecutive threads walk the operand's unit-stride index.
-template <typename T, int ROWS>
-__device__ __forceinline__ void load_tile(float (*s)[ROWS + GF_PAD], const T* A, int64_t sm, int64_t sk,
-                                          int m0, int k0, int M, int K, int tid) {
-  constexpr int N = ROWS * GF_BK;
-  if (sk == 1) {
-#pragma unroll 4
-    for (int e = tid; e < N; e += GF_THREADS) {
-      int m = e / GF_BK, k = e % GF_BK;
-      int gm = m0 + m, gk = k0 + k;
-      s[k][m] = (gm < M && gk < K) ? ld_elem<T>(A + gm * sm + gk) : 0.f;
-    }
-  } else {
-#pragma unroll 4
-    for (int e = tid; e < N; e += GF_THREADS) {
-      int k = e / ROWS, m = e % ROWS;
-      int gm = m0 + m, gk = k0 + k;
-      s[k][m] = (gm < M && gk < K) ? ld_elem<T>(A + gm * sm + (int64_t)gk * sk) : 0.f;
-    }
-  }
-}
-
-template <typename TA, typename TB, typename TO>
-__global__ __launch_bounds__(GF_THREADS) void k_gemm_f32(GemmF32Args g) {
-  __shared__ float As[GF_BK][GF_BM + GF_PAD];
-  __shared__ float Bs[GF_BK][GF_BN + GF_PAD];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int wm = wave >> 1, wn = wave & 1;  // 2 x 2 waves, 64 x 64 each
-  const int b = blockIdx.z;
-  const int m0 = blockIdx.x * GF_BM, n0 = blockIdx.y * GF_BN;
-  const TA* A = (const TA*)g.A + b * g.sAb;
-  const TB* B = (const TB*)g.B + b * g.sBb;
-
-  f32x16_t acc[2][2];
-#pragma unroll
-  for (int i = 0; i < 2; ++i)
-#pragma unroll
-    for (int j = 0; j < 2; ++j) acc[i][j] = f32x16_t{};
-
-  for (int k0 = 0; k0 < g.K; k0 += GF_BK) {
-    load_tile<TA, GF_BM>(As, A, g.sAm, g.sAk, m0, k0, g.M, g.K, tid);
-    // B is addressed as element (k,n) at B + k*sBk + n*sBn; load it as the
-    // tile of B^T (rows n, cols k).
-    load_tile<TB, GF_BN>(Bs, B, g.sBn, g.sBk, n0, k0, g.N, g.K, tid);
-    __syncthreads();
-#pragma unroll
-    for (int kk = 0; kk < GF_BK; kk += 2) {
-      float a[2], bb[2];
-#pragma unroll
-      for (int i = 0; i < 2; ++i) a[i] = As[kk + (lane >> 5)][wm * 64 + i * 32 + (lane & 31)];
-#pragma unroll
-      for (int j = 0; j < 2; ++j) bb[j] = Bs[kk + (lane >> 5)][wn * 64 + j * 32 + (lane & 31)];
-#pragma unroll
-      for (int i = 0; i < 2; ++i)
-#pragma unroll
-        for (int j = 0; j < 2; ++j) acc[i][j] = mfma32x32x2f32(a[i], bb[j], acc[i][j]);
-    }
-    __syncthreads();
-  }
-
-  const float alpha = g.alpha * (g.alpha_ptr ? g.alpha_ptr[b] : 1.f);
-  const float beta = g.beta * (g.beta_ptr ? g.beta_ptr[b] : 1.f);
-  const float* Cin = g.Cin ? g.Cin + b * g.sCinb : nullptr;
-  TO* C = (TO*)g.C + b * g.sCb;
-#pragma unroll
-  for (int i = 0; i < 2; ++i)
-#pragma unroll
-    for (int j = 0; j < 2; ++j)
-#pragma unroll
-      for (int e = 0; e < 16; ++e) {
-        int m = m0 + wm * 64 + i * 32 + acc_row(e, lane);
-        int n = n0 + wn * 64 + j * 32 + (lane & 31);
-        if (m < g.M && n < g.N) {
-          float v = alpha * acc[i][j][e];
-          if (Cin && beta != 0.f) v += beta * Cin[m * g.sCinm + n * g.sCinn];
-          if (m == n) v += g.diag;
-          if constexpr (sizeof(TO) == 4)
-            C[m * g.sCm + n * g.sCn] = v;
-          else
-            C[m * g.sCm + n * g.sCn] = (TO)f2bf(v);
-        }
-      }
-}
-
-
-// Pipelined variant for the aligned case (every operand has a unit-stride
-// dimension, the other stride and that dimension's extent multiples of 4,
-// 16-byte (fp32) or 8-byte (bf16) aligned bases): 128 x 128 tiles, K staged
+// The aligned case (every operand has a unit-stride dimension, the other
+// stride and that dimension's extent multiples of 4, 16-byte aligned bases):
+// 128 x 128 tiles, K staged
 // 32 at a time with 16-byte global loads into registers one stage ahead and
 // two LDS buffers, so the matrix units work on one stage while the next is
 // in flight (one barrier per stage).  A is either m-contiguous (AK = false:
@@ -214,7 +119,7 @@ __device__ __forceinline__ void sk_run(const GemmF32Args& g, F&& products, int t
 // read in full before the first store: C may alias Cin as far as the
 // compiler knows, which would otherwise hold every load behind the store
 // before it.
-template <typename TO, int F = 2>
+template <int F = 2>
 __device__ __forceinline__ void gv_epilogue(const GemmF32Args& g, const f32x16_t (&acc)[F][F], int b, int tbm,
                                             int tbn, int lane, int wm, int wn) {
   const int m0 = (tbm * 2 + wm) * 32 * F, n0 = (tbn * 2 + wn) * 32 * F;
@@ -237,7 +142,7 @@ __device__ __forceinline__ void gv_epilogue(const GemmF32Args& g, const f32x16_t
           cin[i][j][e] = (m < g.M && n < g.N) ? Cin[m * g.sCinm + n * g.sCinn] : 0.f;
         }
   }
-  TO* C = (TO*)Cbase + b * g.sCb;
+  float* C = (float*)Cbase + b * g.sCb;
 #pragma unroll
   for (int i = 0; i < F; ++i)
 #pragma unroll
@@ -249,50 +154,30 @@ __device__ __forceinline__ void gv_epilogue(const GemmF32Args& g, const f32x16_t
           float v = alpha * acc[i][j][e];
           if (has_cin) v += beta * cin[i][j][e];
           if (m == n) v += g.diag;
-          if constexpr (sizeof(TO) == 4) {
-            C[m * g.sCm + n * g.sCn] = v;
-            if (g.sym_upper && tbm != tbn) C[n * g.sCm + m * g.sCn] = v;
-          } else {
-            C[m * g.sCm + n * g.sCn] = (TO)f2bf(v);
-            if (g.sym_upper && tbm != tbn) C[n * g.sCm + m * g.sCn] = (TO)f2bf(v);
-          }
+          C[m * g.sCm + n * g.sCn] = v;
+          if (g.sym_upper && tbm != tbn) C[n * g.sCm + m * g.sCn] = v;
         }
       }
 }
 
 // Operand loads are raw buffer loads (out-of-range offsets read zero) into
-// registers that are converted to fp32 only when the stage is written to LDS,
-// so nothing waits for the loads before the products of the current stage.
+// registers that are read only when the stage is written to LDS, so nothing
+// waits for the loads before the products of the current stage.
 constexpr uint32_t GV_OOB = 0x80000000u;  // any offset >= num_records reads zero
 
-template <typename T>
-struct Raw4;  // four consecutive elements as loaded
-template <>
-struct Raw4<float> {
-  typedef __attribute__((ext_vector_type(4))) uint32_t type;
-  static __device__ __forceinline__ type load(__amdgpu_buffer_rsrc_t r, uint32_t off) {
-    return __builtin_amdgcn_raw_buffer_load_b128(r, off, 0, 0);
-  }
-  static __device__ __forceinline__ float4 cvt(type v) {
-    return make_float4(__uint_as_float(v[0]), __uint_as_float(v[1]), __uint_as_float(v[2]), __uint_as_float(v[3]));
-  }
-};
-template <>
-struct Raw4<bf16_t> {
-  typedef __attribute__((ext_vector_type(2))) uint32_t type;
-  static __device__ __forceinline__ type load(__amdgpu_buffer_rsrc_t r, uint32_t off) {
-    return __builtin_amdgcn_raw_buffer_load_b64(r, off, 0, 0);
-  }
-  static __device__ __forceinline__ float4 cvt(type v) {
-    return make_float4(bf2f(v[0] & 0xFFFFu), bf2f(v[0] >> 16), bf2f(v[1] & 0xFFFFu), bf2f(v[1] >> 16));
-  }
-};
+typedef __attribute__((ext_vector_type(4))) uint32_t raw4_t;  // four consecutive floats as loaded
+__device__ __forceinline__ raw4_t raw4_load(__amdgpu_buffer_rsrc_t r, uint32_t off) {
+  return __builtin_amdgcn_raw_buffer_load_b128(r, off, 0, 0);
+}
+__device__ __forceinline__ float4 raw4_f(raw4_t v) {
+  return make_float4(__uint_as_float(v[0]), __uint_as_float(v[1]), __uint_as_float(v[2]), __uint_as_float(v[3]));
+}
 
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t gv_rsrc(const void* base, int64_t bytes) {
   return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), 0, (int)(bytes > 0 ? bytes : 0), 0x00020000);
 }
 
-template <typename TA, typename TB, typename TO, bool AK>
+template <bool AK>
 __global__ __launch_bounds__(GF_THREADS) void k_gemm_f32v(GemmF32Args g) {
   __shared__ __attribute__((aligned(16))) float As[2][GV_BK / 2][GV_BM][2];
   __shared__ __attribute__((aligned(16))) float Bs[2][GV_BK / 2][GV_BN][2];
@@ -304,16 +189,16 @@ __global__ __launch_bounds__(GF_THREADS) void k_gemm_f32v(GemmF32Args g) {
   const int m0 = tbm * GV_BM, n0 = tbn * GV_BN;
   // the host guarantees that each operand's extent fits 31-bit byte offsets
   const __amdgpu_buffer_rsrc_t rA =
-      gv_rsrc((const TA*)g.A + b * g.sAb,
-              (AK ? (int64_t)(g.M - 1) * g.sAm + g.K : (int64_t)(g.K - 1) * g.sAk + g.M) * (int64_t)sizeof(TA));
+      gv_rsrc((const float*)g.A + b * g.sAb,
+              (AK ? (int64_t)(g.M - 1) * g.sAm + g.K : (int64_t)(g.K - 1) * g.sAk + g.M) * 4);
   const __amdgpu_buffer_rsrc_t rB =
-      gv_rsrc((const TB*)g.B + b * g.sBb, ((int64_t)(g.K - 1) * g.sBk + g.N) * (int64_t)sizeof(TB));
+      gv_rsrc((const float*)g.B + b * g.sBb, ((int64_t)(g.K - 1) * g.sBk + g.N) * 4);
 
   // per thread and stage: B (and an m-contiguous A) as two k-pairs of four
   // consecutive columns ([pair][row of the pair]); a k-contiguous A as four
   // runs of four k
-  typename Raw4<TA>::type ra[4];
-  typename Raw4<TB>::type rb[4];
+  raw4_t ra[4];
+  raw4_t rb[4];
   auto load = [&](int k0) {
 #pragma unroll
     for (int v = 0; v < 2; ++v) {
@@ -322,14 +207,14 @@ __global__ __launch_bounds__(GF_THREADS) void k_gemm_f32v(GemmF32Args g) {
 #pragma unroll
       for (int h = 0; h < 2; ++h) {
         const bool ok = k + h < g.K && n < g.N;
-        rb[2 * v + h] = Raw4<TB>::load(rB, ok ? (uint32_t)(((int64_t)(k + h) * g.sBk + n) * sizeof(TB)) : GV_OOB);
+        rb[2 * v + h] = raw4_load(rB, ok ? (uint32_t)(((int64_t)(k + h) * g.sBk + n) * 4) : GV_OOB);
       }
       if constexpr (!AK) {
         const int m = m0 + 4 * (idx & 31);
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
           const bool ok = k + h < g.K && m < g.M;
-          ra[2 * v + h] = Raw4<TA>::load(rA, ok ? (uint32_t)(((int64_t)(k + h) * g.sAk + m) * sizeof(TA)) : GV_OOB);
+          ra[2 * v + h] = raw4_load(rA, ok ? (uint32_t)(((int64_t)(k + h) * g.sAk + m) * 4) : GV_OOB);
         }
       }
     }
@@ -339,7 +224,7 @@ __global__ __launch_bounds__(GF_THREADS) void k_gemm_f32v(GemmF32Args g) {
         const int idx = tid + GF_THREADS * v;  // m = idx / 8, k = 4 (idx % 8) .. +3
         const int m = m0 + (idx >> 3), k = k0 + 4 * (idx & 7);
         const bool ok = m < g.M && k < g.K;
-        ra[v] = Raw4<TA>::load(rA, ok ? (uint32_t)(((int64_t)m * g.sAm + k) * sizeof(TA)) : GV_OOB);
+        ra[v] = raw4_load(rA, ok ? (uint32_t)(((int64_t)m * g.sAm + k) * 4) : GV_OOB);
       }
     }
   };
@@ -348,13 +233,13 @@ __global__ __launch_bounds__(GF_THREADS) void k_gemm_f32v(GemmF32Args g) {
     for (int v = 0; v < 2; ++v) {
       const int idx = tid + GF_THREADS * v;
       const int kp = idx >> 5, c4 = 4 * (idx & 31), sw = (idx & 31) >> 3;
-      const float4 r0 = Raw4<TB>::cvt(rb[2 * v]), r1 = Raw4<TB>::cvt(rb[2 * v + 1]);
+      const float4 r0 = raw4_f(rb[2 * v]), r1 = raw4_f(rb[2 * v + 1]);
       *(float2*)&Bs[buf][kp][c4 + (0 ^ sw)][0] = make_float2(r0.x, r1.x);
       *(float2*)&Bs[buf][kp][c4 + (1 ^ sw)][0] = make_float2(r0.y, r1.y);
       *(float2*)&Bs[buf][kp][c4 + (2 ^ sw)][0] = make_float2(r0.z, r1.z);
       *(float2*)&Bs[buf][kp][c4 + (3 ^ sw)][0] = make_float2(r0.w, r1.w);
       if constexpr (!AK) {
-        const float4 a0 = Raw4<TA>::cvt(ra[2 * v]), a1 = Raw4<TA>::cvt(ra[2 * v + 1]);
+        const float4 a0 = raw4_f(ra[2 * v]), a1 = raw4_f(ra[2 * v + 1]);
         *(float2*)&As[buf][kp][c4 + (0 ^ sw)][0] = make_float2(a0.x, a1.x);
         *(float2*)&As[buf][kp][c4 + (1 ^ sw)][0] = make_float2(a0.y, a1.y);
         *(float2*)&As[buf][kp][c4 + (2 ^ sw)][0] = make_float2(a0.z, a1.z);
@@ -366,7 +251,7 @@ __global__ __launch_bounds__(GF_THREADS) void k_gemm_f32v(GemmF32Args g) {
       for (int v = 0; v < 4; ++v) {
         const int idx = tid + GF_THREADS * v;
         const int m = (idx >> 3) ^ ((idx & 7) << 2), kp = 2 * (idx & 7);
-        const float4 a = Raw4<TA>::cvt(ra[v]);
+        const float4 a = raw4_f(ra[v]);
         *(float2*)&As[buf][kp][m][0] = make_float2(a.x, a.y);
         *(float2*)&As[buf][kp + 1][m][0] = make_float2(a.z, a.w);
       }
@@ -413,7 +298,7 @@ __global__ __launch_bounds__(GF_THREADS) void k_gemm_f32v(GemmF32Args g) {
   gv_tile(g, tbm, tbn, b);
   f32x16_t acc[2][2];
   products(b, tbm, tbn, 0, nk, acc);
-  gv_epilogue<TO>(g, acc, b, tbm, tbn, lane, wm, wn);
+  gv_epilogue<>(g, acc, b, tbm, tbn, lane, wm, wn);
 }
 
 // Split variant of the aligned fp32 GEMM (fp32 operands and output): the
@@ -469,7 +354,7 @@ __global__ __launch_bounds__(GF_THREADS) __attribute__((amdgpu_waves_per_eu(256 
       gv_rsrc((const float*)(second ? g.A2 : g.A) + e * g.sAb,
               (AK ? (int64_t)(g.M - 1) * g.sAm + g.K : (int64_t)(g.K - 1) * g.sAk + g.M) * 4);
   const __amdgpu_buffer_rsrc_t rB = gv_rsrc((const float*)g.B + e * g.sBb, ((int64_t)(g.K - 1) * g.sBk + g.N) * 4);
-  typedef Raw4<float>::type raw_t;
+  typedef raw4_t raw_t;
   // two register sets: the loads of stages it + 1 and it + 2 are in flight
   // while stage it is multiplied
   raw_t ra0[4], rb0[4], ra1[4], rb1[4];
@@ -481,15 +366,15 @@ __global__ __launch_bounds__(GF_THREADS) __attribute__((amdgpu_waves_per_eu(256 
 #pragma unroll
     for (int h = 0; h < KPT; ++h) {
       const int k = kb + h;
-      rb[h] = Raw4<float>::load(rB, (k < g.K && n0 + c < g.N) ? (uint32_t)(((int64_t)k * g.sBk + n0 + c) * 4) : GV_OOB);
+      rb[h] = raw4_load(rB, (k < g.K && n0 + c < g.N) ? (uint32_t)(((int64_t)k * g.sBk + n0 + c) * 4) : GV_OOB);
       if constexpr (!AK)
-        ra[h] = Raw4<float>::load(rA, (k < g.K && m0 + c < g.M) ? (uint32_t)(((int64_t)k * g.sAk + m0 + c) * 4) : GV_OOB);
+        ra[h] = raw4_load(rA, (k < g.K && m0 + c < g.M) ? (uint32_t)(((int64_t)k * g.sAk + m0 + c) * 4) : GV_OOB);
     }
     if constexpr (AK) {
       const int m = m0 + tid / TPR, k = k0 + 4 * KQ * (tid % TPR);
 #pragma unroll
       for (int h = 0; h < KQ; ++h)
-        ra[h] = Raw4<float>::load(rA, (m < g.M && k + 4 * h < g.K) ? (uint32_t)(((int64_t)m * g.sAm + k + 4 * h) * 4)
+        ra[h] = raw4_load(rA, (m < g.M && k + 4 * h < g.K) ? (uint32_t)(((int64_t)m * g.sAm + k + 4 * h) * 4)
                                                                     : GV_OOB);
     }
   };
@@ -607,7 +492,7 @@ __global__ __launch_bounds__(GF_THREADS) __attribute__((amdgpu_waves_per_eu(256 
   gv_tile<BT>(g, tbm, tbn, b);
   f32x16_t acc[F][F];
   products(b, tbm, tbn, 0, nk, acc);
-  gv_epilogue<float, F>(g, acc, b, tbm, tbn, lane, wm, wn);
+  gv_epilogue<F>(g, acc, b, tbm, tbn, lane, wm, wn);
 }
 
 // The stream-K fix-up: one workgroup per (tile, wave quarter), one wave per
@@ -655,33 +540,32 @@ __global__ __launch_bounds__(256) void k_gemm_sk_fix(GemmF32Args g) {
 }
 
 // The aligned case of the pipelined kernel: returns 0 (A m-contiguous), 1
-// (A k-contiguous) or -1 (use the general kernel).
-int gemm_f32_vec_mode(const GemmF32Args& g, int ta, int tb) {
-  const int ea = ta ? 2 : 4, eb = tb ? 2 : 4;
-  auto al = [](const void* p, int e) { return ((uintptr_t)p % (uintptr_t)(4 * e)) == 0; };
+// (A k-contiguous) or -1 (neither).
+int gemm_f32_vec_mode(const GemmF32Args& g) {
+  auto al = [](const void* p) { return ((uintptr_t)p % 16) == 0; };
   auto m4 = [](int64_t v) { return v % 4 == 0; };
-  if (g.K <= 0 || !al(g.A, ea) || !al(g.B, eb)) return -1;
+  if (g.K <= 0 || !al(g.A) || !al(g.B)) return -1;
   if (!(g.sBn == 1 && m4(g.sBk) && m4(g.N) && m4(g.sBb))) return -1;
   // buffer offsets are 31-bit byte offsets
   const int64_t lim = 0x7fffffffll - 16;
-  if (((int64_t)(g.K - 1) * g.sBk + g.N) * eb > lim) return -1;
-  if (g.sAm == 1 && m4(g.sAk) && m4(g.M) && m4(g.sAb) && ((int64_t)(g.K - 1) * g.sAk + g.M) * ea <= lim) return 0;
-  if (g.sAk == 1 && m4(g.sAm) && m4(g.K) && m4(g.sAb) && ((int64_t)(g.M - 1) * g.sAm + g.K) * ea <= lim) return 1;
+  if (((int64_t)(g.K - 1) * g.sBk + g.N) * 4 > lim) return -1;
+  if (g.sAm == 1 && m4(g.sAk) && m4(g.M) && m4(g.sAb) && ((int64_t)(g.K - 1) * g.sAk + g.M) * 4 <= lim) return 0;
+  if (g.sAk == 1 && m4(g.sAm) && m4(g.K) && m4(g.sAb) && ((int64_t)(g.M - 1) * g.sAm + g.K) * 4 <= lim) return 1;
   return -1;
 }
 
 }  // namespace
 
-hipError_t launch_gemm_f32(const GemmF32Args& g, int ta, int tb, int to, hipStream_t s) {
+hipError_t launch_gemm_f32(const GemmF32Args& g, hipStream_t s) {
   if (g.M <= 0 || g.N <= 0 || g.batch <= 0) return hipSuccess;
-  const int vm = gemm_f32_vec_mode(g, ta, tb);
-  if (g.sym_upper && (vm < 0 || g.M != g.N)) return hipErrorInvalidValue;
+  const int vm = gemm_f32_vec_mode(g);
+  if (g.sym_upper && g.M != g.N) return hipErrorInvalidValue;
   if (g.sk_part && g.Cin) return hipErrorInvalidValue;  // the fix-up applies no Cin
   if (g.split < 0 || g.split > GEMM_SPLIT_F16) return hipErrorInvalidValue;
   if ((g.pre_a || g.pre_b) && g.split != GEMM_SPLIT_F16) return hipErrorInvalidValue;
   if (g.A2 && (g.split != GEMM_SPLIT_F16 || !g.C2 || g.sk_part || g.bsplit <= 0 || g.bsplit >= g.batch))
     return hipErrorInvalidValue;
-  if (g.sk_part && !(g.sym_upper && ta == 0 && tb == 0 && to == 0)) return hipErrorInvalidValue;
+  if (g.sk_part && !g.sym_upper) return hipErrorInvalidValue;
   const int ntm = (g.M + GV_BM - 1) / GV_BM;
   const dim3 vgrid = g.sk_part      ? dim3(gemm_f32_sk_plan(g.M, g.K, g.batch).nwg)
                      : g.sym_upper ? dim3(ntm * (ntm + 1) / 2, 1, g.batch)
@@ -691,7 +575,7 @@ hipError_t launch_gemm_f32(const GemmF32Args& g, int ta, int tb, int to, hipStre
     hipLaunchKernelGGL(k_gemm_sk_fix, dim3(4 * gemm_f32_sk_plan(g.M, g.K, g.batch).T), dim3(256), 0, s, g);
     return hipGetLastError();
   };
-  if (g.split && (vm < 0 || ta || tb || to)) return hipErrorInvalidValue;
+  if (g.split && vm < 0) return hipErrorInvalidValue;
   if (g.split == GEMM_SPLIT_F16) {
     // 64 x 64 tiles where 128 x 128 ones would give fewer than X3_SMALL_BELOW
     // workgroups: such launches are bound by one workgroup's latency, and
@@ -711,43 +595,23 @@ hipError_t launch_gemm_f32(const GemmF32Args& g, int ta, int tb, int to, hipStre
     const hipError_t e = hipGetLastError();
     return e != hipSuccess ? e : sk_fix();
   }
-  if (vm >= 0) {
-    const dim3 grid = vgrid;
-#define MAPL_GV(TA_, TB_, TO_)                                                                        \
-  do {                                                                                                \
-    if (vm)                                                                                           \
-      hipLaunchKernelGGL((k_gemm_f32v<TA_, TB_, TO_, true>), grid, dim3(GF_THREADS), 0, s, g);        \
-    else                                                                                              \
-      hipLaunchKernelGGL((k_gemm_f32v<TA_, TB_, TO_, false>), grid, dim3(GF_THREADS), 0, s, g);       \
-  } while (0)
-    if (ta == 0 && tb == 0 && to == 0) MAPL_GV(float, float, float);
-    else if (ta == 1 && tb == 0 && to == 0) MAPL_GV(bf16_t, float, float);
-    else if (ta == 0 && tb == 1 && to == 0) MAPL_GV(float, bf16_t, float);
-    else if (ta == 1 && tb == 1 && to == 0) MAPL_GV(bf16_t, bf16_t, float);
-    else if (ta == 1 && tb == 1 && to == 1) MAPL_GV(bf16_t, bf16_t, bf16_t);
-    else if (ta == 0 && tb == 0 && to == 1) MAPL_GV(float, float, bf16_t);
-    else if (ta == 1 && tb == 0 && to == 1) MAPL_GV(bf16_t, float, bf16_t);
-    else if (ta == 0 && tb == 1 && to == 1) MAPL_GV(float, bf16_t, bf16_t);
-    else return hipErrorInvalidValue;
-#undef MAPL_GV
-    const hipError_t e = hipGetLastError();
-    return e != hipSuccess ? e : sk_fix();
+  // few tiles (a launch bound by one workgroup's walk over K), or strides the
+  // vector loads do not take
+  if (vm < 0 || gemm_f32_small(g.M, g.N, g.batch)) {
+    if (g.alpha_ptr || g.beta_ptr) return hipErrorInvalidValue;
+    GemmF32sArgs q{};
+    q.nseg = 1;
+    q.seg[0] = {(const float*)g.A, g.sAm, g.sAk, (const float*)g.B, g.sBk, g.sBn, g.K, nullptr, 0, 0, 1.f};
+    q.M = g.M; q.N = g.N; q.batch = g.batch; q.sAb = g.sAb; q.sBb = g.sBb;
+    q.Cin = g.beta != 0.f ? g.Cin : nullptr; q.sCinm = g.sCinm; q.sCinn = g.sCinn; q.sCinb = g.sCinb;
+    q.C = (float*)g.C; q.sCm = g.sCm; q.sCn = g.sCn; q.sCb = g.sCb;
+    q.alpha = g.alpha; q.beta = g.beta; q.diag = g.diag; q.sym_upper = g.sym_upper;
+    return launch_gemm_f32s(q, s);
   }
-  if (g.sk_part) return hipErrorInvalidValue;
-  dim3 grid((g.M + GF_BM - 1) / GF_BM, (g.N + GF_BN - 1) / GF_BN, g.batch);
-  dim3 block(GF_THREADS);
-#define MAPL_GF(TA_, TB_, TO_) hipLaunchKernelGGL((k_gemm_f32<TA_, TB_, TO_>), grid, block, 0, s, g)
-  if (ta == 0 && tb == 0 && to == 0) MAPL_GF(float, float, float);
-  else if (ta == 1 && tb == 0 && to == 0) MAPL_GF(bf16_t, float, float);
-  else if (ta == 0 && tb == 1 && to == 0) MAPL_GF(float, bf16_t, float);
-  else if (ta == 1 && tb == 1 && to == 0) MAPL_GF(bf16_t, bf16_t, float);
-  else if (ta == 1 && tb == 1 && to == 1) MAPL_GF(bf16_t, bf16_t, bf16_t);
-  else if (ta == 0 && tb == 0 && to == 1) MAPL_GF(float, float, bf16_t);
-  else if (ta == 1 && tb == 0 && to == 1) MAPL_GF(bf16_t, float, bf16_t);
-  else if (ta == 0 && tb == 1 && to == 1) MAPL_GF(float, bf16_t, bf16_t);
-  else return hipErrorInvalidValue;
-#undef MAPL_GF
-  return hipGetLastError();
+  if (vm) hipLaunchKernelGGL(k_gemm_f32v<true>, vgrid, dim3(GF_THREADS), 0, s, g);
+  else hipLaunchKernelGGL(k_gemm_f32v<false>, vgrid, dim3(GF_THREADS), 0, s, g);
+  const hipError_t e = hipGetLastError();
+  return e != hipSuccess ? e : sk_fix();
 }
 
 }  // namespace mapl

@@ -9,14 +9,6 @@ namespace mapl {
 
 namespace {
 
-__global__ void k_gather_rows_f32(const float* __restrict__ A, int k, const int32_t* __restrict__ ids,
-                                  int V, int T, float* __restrict__ out) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= (int64_t)T * k) return;
-  const int t = (int)(i / k), c = (int)(i % k);
-  out[i] = A[(int64_t)clamp_id(ids[t], V) * k + c];
-}
-
 // One wave per token: residual in registers/LDS, exact fp32 squared
 // distances sum_c (R_c - C_jc)^2 for every codeword, lowest index on ties.
 __global__ void k_rvq_f32(const float* __restrict__ Z0, const float* __restrict__ C, int T, int r, int L,
@@ -233,14 +225,6 @@ __global__ void k_codebook_unpack(const float* __restrict__ buf, const int32_t* 
 }
 
 }  // namespace
-
-hipError_t launch_gather_rows_f32(const float* A, int k, const int32_t* ids, int V, int T, float* out,
-                                  hipStream_t s) {
-  const int64_t n = (int64_t)T * k;
-  if (n <= 0) return hipSuccess;
-  hipLaunchKernelGGL(k_gather_rows_f32, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, A, k, ids, V, T, out);
-  return hipGetLastError();
-}
 
 hipError_t launch_rvq_f32(const float* Z0, const float* C, int T, int r, int L, int K, void* codes,
                           int code_bytes, hipStream_t s) {

@@ -34,8 +34,7 @@ hipError_t launch_gemm_tn(const TnArgs& g, hipStream_t s);
 bool gemm_tn_gathers(const TnArgs& g);
 
 // ---------------------------------------------------------------- fp32 GEMM
-// C[b](m,n) = alpha_b sum_k A[b](m,k) B[b](k,n) + beta_b Cin[b](m,n)
-// element types: 0 = fp32, 1 = bf16 (A, B, C); Cin is fp32 (may be null).
+// C[b](m,n) = alpha_b sum_k A[b](m,k) B[b](k,n) + beta_b Cin[b](m,n), all fp32; Cin may be null.
 enum { GEMM_SPLIT_NONE = 0, GEMM_SPLIT_F16 = 1 };
 struct GemmF32Args {
   const void* A; int64_t sAm, sAk, sAb;
@@ -46,7 +45,7 @@ struct GemmF32Args {
   float alpha, beta;
   const float* alpha_ptr; const float* beta_ptr;
   float diag;  // added to every element with m == n after the scaling
-  int split;  // fp32 operands and output, aligned: GEMM_SPLIT_F16 takes the products as
+  int split;  // aligned operands: GEMM_SPLIT_F16 takes the products as
              // hi.hi + hi.lo + lo.hi of fp16 pieces of 2^8 x (|operands| < 255)
   const float* pre_a; const float* pre_b;  // GEMM_SPLIT_F16 only: per-batch factors of A and B
                                            // (null: 1), applied before the split
@@ -57,11 +56,36 @@ struct GemmF32Args {
   int sym_upper;   // C = A B known symmetric (M == N; Cin, if any, symmetric too): only tiles on or
                    // above the diagonal are computed, each off-diagonal one also written mirrored
                    // (aligned case)
-  float* sk_part;  // sym_upper, fp32 operands and output: with this workspace (gemm_f32_sk_bytes)
+  float* sk_part;  // sym_upper: with this workspace (gemm_f32_sk_bytes)
                    // the tiles' K ranges are split evenly over two workgroups per CU (stream-K) and
                    // a second launch sums each tile's pieces in K order
 };
-hipError_t launch_gemm_f32(const GemmF32Args& g, int ta, int tb, int to, hipStream_t s);
+hipError_t launch_gemm_f32(const GemmF32Args& g, hipStream_t s);
+
+// Latency-bound fp32 products (few 128 x 128 output tiles):
+//   C[b](m,n) = alpha sum_s sign_s sum_k A_s(m,k) B_s(k,n) + beta Cin[b](m,n)
+// over one or two segments s, any strides.  A segment's A may be gathered from
+// a table by token id: gather 1, A_s(m,k) = A[ids[m] sAm + k sAk]; gather 2,
+// A_s(m,k) = A[m sAm + ids[k] sAk]; ids outside [0, V) read row 0.  Batches
+// (sAb, sBb) apply to segment 0.  sym_upper as in GemmF32Args.
+struct GemmF32Seg {
+  const float* A; int64_t sAm, sAk;
+  const float* B; int64_t sBk, sBn;
+  int K;
+  const int32_t* ids; int gather, V;
+  float sign;
+};
+struct GemmF32sArgs {
+  GemmF32Seg seg[2]; int nseg;
+  int M, N, batch; int64_t sAb, sBb;
+  const float* Cin; int64_t sCinm, sCinn, sCinb;
+  float* C; int64_t sCm, sCn, sCb;
+  float alpha, beta, diag;
+  int sym_upper;
+};
+// Whether launch_gemm_f32s is the better kernel for an M x N x batch output.
+bool gemm_f32_small(int64_t M, int64_t N, int64_t batch);
+hipError_t launch_gemm_f32s(const GemmF32sArgs& g, hipStream_t s);
 
 // Stream-K plan of a symmetric product (M x M output, upper 128 x 128 tiles
 // of batch entries, K in 32-deep stages): T tiles, nk stages each, runs of U
@@ -217,9 +241,6 @@ bool enc_rvq_fusable(int r, int L);
 hipError_t launch_enc_rvq(const TnArgs& g, const RvqArgs& a, hipStream_t s);
 
 // ---------------------------------------------------------------- fp32 codec path helpers
-// out[t][i] = A[ids[t]][i] (fp32) for i < k.
-hipError_t launch_gather_rows_f32(const float* A, int k, const int32_t* ids, int V, int T, float* out,
-                                  hipStream_t s);
 // fp32 residual quantisation with exact fp32 distances over all K.
 hipError_t launch_rvq_f32(const float* Z0, const float* C, int T, int r, int L, int K, void* codes,
                           int code_bytes, hipStream_t s);

@@ -231,20 +231,17 @@ Layout layout(const mapl_codec_desc& D, int call, const GradQ* q = nullptr) {
   } else {
     switch (call) {
       case MAPL_CALL_ENCODE:
-        if (k > 0) Lo.ga = c.take((size_t)T * k * 4);
         if (k > 0 && amb) Lo.bu = c.take((size_t)k * r * 4);
         if (D.L > 0) Lo.z0 = c.take((size_t)T * r * 4);
         break;
       case MAPL_CALL_DECODE:
       case MAPL_CALL_DECODE_BWD:
-        if (k > 0) Lo.ga = c.take((size_t)T * k * 4);
         Lo.zh = c.take((size_t)T * r * 4);
         if (!amb && k > 0) Lo.z2 = c.take((size_t)T * r * 4);
         if (q && call == MAPL_CALL_DECODE_BWD) Lo.z0 = c.take((size_t)T * r * 4);
         break;
       case MAPL_CALL_ENCODE_BWD:
         if (k > 0 && amb) {
-          Lo.ga = c.take((size_t)T * k * 4);
           Lo.wsum = c.take((size_t)k * r * 4);
         }
         break;
@@ -347,6 +344,24 @@ GemmF32Args gemm(int M, int N, int K) {
   g.M = M; g.N = N; g.K = K; g.batch = 1;
   g.alpha = 1.f; g.beta = 0.f;
   return g;
+}
+
+// The latency-bound fp32 product's builders: an M x N output of row stride ldc
+// and its segments (see GemmF32Seg).
+GemmF32sArgs gemm_s(int64_t M, int64_t N, void* C, int64_t ldc) {
+  GemmF32sArgs g;
+  memset(&g, 0, sizeof g);
+  g.M = (int)M; g.N = (int)N; g.batch = 1;
+  g.C = (float*)C; g.sCm = ldc; g.sCn = 1;
+  g.alpha = 1.f;
+  return g;
+}
+void add_seg(GemmF32sArgs& g, const void* A, int64_t sAm, int64_t sAk, const void* B, int64_t sBk, int64_t sBn,
+             int64_t K, float sign = 1.f, const int32_t* ids = nullptr, int gather = 0, int64_t V = 0) {
+  g.seg[g.nseg++] = {(const float*)A, sAm, sAk, (const float*)B, sBk, sBn, (int)K, ids, gather, (int)V, sign};
+}
+void add_cin(GemmF32sArgs& g, const float* Cin, int64_t ld) {
+  g.Cin = Cin; g.sCinm = ld; g.sCinn = 1; g.beta = 1.f;
 }
 
 template <typename P>
@@ -488,34 +503,31 @@ extern "C" int mapl_encode(const mapl_codec_desc* desc, const void* X, const int
 
   // ---------------- fp32 path
   float* out = D.L == 0 ? (float*)payload : at<float>(ws, Lo.z0);
-  {
+  const float* Bk = (const float*)B_s;  // coord: [k,r]
+  if (k > 0 && amb) {
+    float* BU = at<float>(ws, Lo.bu);
+    GemmF32Args g = gemm((int)k, (int)r, (int)d);
+    g.A = B_s; g.sAm = d; g.sAk = 1;
+    g.B = U; g.sBk = r; g.sBn = 1;
+    g.C = BU; g.sCm = r; g.sCn = 1;
+    LAUNCH("enc:gemm_f32", launch_gemm_f32(g, s));
+    Bk = BU;
+  }
+  // X U and -A_s[ids] Bk in one launch where the output is small, else the
+  // second added to the first
+  GemmF32sArgs q = gemm_s(T, r, out, r);
+  if (gemm_f32_small(T, r, 1)) {
+    add_seg(q, X, d, 1, U, r, 1, d);
+  } else {
     GemmF32Args g = gemm((int)T, (int)r, (int)d);
     g.A = X; g.sAm = d; g.sAk = 1;
     g.B = U; g.sBk = r; g.sBn = 1;
     g.C = out; g.sCm = r; g.sCn = 1;
-    LAUNCH("enc:gemm_f32", launch_gemm_f32(g, 0, 0, 0, s));
+    LAUNCH("enc:gemm_f32", launch_gemm_f32(g, s));
+    add_cin(q, out, r);
   }
-  if (k > 0) {
-    float* a = at<float>(ws, Lo.ga);
-    LAUNCH("enc:gather_rows_f32", launch_gather_rows_f32((const float*)A_s, (int)k, ids, (int)D.V, (int)T, a, s));
-    const float* Bk = (const float*)B_s;  // coord: [k,r]
-    if (amb) {
-      float* BU = at<float>(ws, Lo.bu);
-      GemmF32Args g = gemm((int)k, (int)r, (int)d);
-      g.A = B_s; g.sAm = d; g.sAk = 1;
-      g.B = U; g.sBk = r; g.sBn = 1;
-      g.C = BU; g.sCm = r; g.sCn = 1;
-      LAUNCH("enc:gemm_f32", launch_gemm_f32(g, 0, 0, 0, s));
-      Bk = BU;
-    }
-    GemmF32Args g = gemm((int)T, (int)r, (int)k);
-    g.A = a; g.sAm = k; g.sAk = 1;
-    g.B = Bk; g.sBk = r; g.sBn = 1;
-    g.Cin = out; g.sCinm = r; g.sCinn = 1;
-    g.C = out; g.sCm = r; g.sCn = 1;
-    g.alpha = -1.f; g.beta = 1.f;
-    LAUNCH("enc:gemm_f32", launch_gemm_f32(g, 0, 0, 0, s));
-  }
+  if (k > 0) add_seg(q, A_s, k, 1, Bk, r, 1, k, -1.f, ids, 1, D.V);
+  if (q.nseg > 0) LAUNCH("enc:gemm_f32s", launch_gemm_f32s(q, s));
   if (grouped(D))
     LAUNCH("enc:grvq", launch_grvq(out, C, (int)T, (int)r, D.L, D.K, (uint8_t*)payload, s));
   else if (D.L > 0)
@@ -597,32 +609,19 @@ extern "C" int mapl_decode(const mapl_codec_desc* desc, const void* payload, con
     LAUNCH("dec:codes_sum_f32", launch_codes_sum_f32(payload, cbytes, C, (int)T, (int)r, D.L, D.K, z, s, grouped(D) ? 2 : 0));
     Zh = z;
   }
-  float* a = k > 0 ? at<float>(ws, Lo.ga) : nullptr;
-  if (k > 0) LAUNCH("dec:gather_rows_f32", launch_gather_rows_f32((const float*)A_r, (int)k, ids, (int)D.V, (int)T, a, s));
   if (!amb && k > 0) {
     float* z2 = at<float>(ws, Lo.z2);
-    GemmF32Args g = gemm((int)T, (int)r, (int)k);
-    g.A = a; g.sAm = k; g.sAk = 1;
-    g.B = B_r; g.sBk = r; g.sBn = 1;
-    g.Cin = Zh; g.sCinm = r; g.sCinn = 1; g.beta = 1.f;
-    g.C = z2; g.sCm = r; g.sCn = 1;
-    LAUNCH("dec:gemm_f32", launch_gemm_f32(g, 0, 0, 0, s));
+    GemmF32sArgs g = gemm_s(T, r, z2, r);
+    add_cin(g, Zh, r);
+    add_seg(g, A_r, k, 1, B_r, r, 1, k, 1.f, ids, 1, D.V);
+    LAUNCH("dec:gemm_f32s", launch_gemm_f32s(g, s));
     Zh = z2;
   }
   {
-    GemmF32Args g = gemm((int)T, (int)d, (int)r);
-    g.A = Zh; g.sAm = r; g.sAk = 1;
-    g.B = U; g.sBk = 1; g.sBn = r;
-    g.C = Xhat; g.sCm = d; g.sCn = 1;
-    LAUNCH("dec:gemm_f32", launch_gemm_f32(g, 0, 0, 0, s));
-  }
-  if (amb && k > 0) {
-    GemmF32Args g = gemm((int)T, (int)d, (int)k);
-    g.A = a; g.sAm = k; g.sAk = 1;
-    g.B = B_r; g.sBk = d; g.sBn = 1;
-    g.Cin = (const float*)Xhat; g.sCinm = d; g.sCinn = 1; g.beta = 1.f;
-    g.C = Xhat; g.sCm = d; g.sCn = 1;
-    LAUNCH("dec:gemm_f32", launch_gemm_f32(g, 0, 0, 0, s));
+    GemmF32sArgs g = gemm_s(T, d, Xhat, d);
+    add_seg(g, Zh, r, 1, U, 1, r, r);
+    if (amb && k > 0) add_seg(g, A_r, k, 1, B_r, d, 1, k, 1.f, ids, 1, D.V);
+    LAUNCH("dec:gemm_f32s", launch_gemm_f32s(g, s));
   }
   return MAPL_OK;
 }
@@ -740,7 +739,7 @@ int decode_bwd_impl(const mapl_codec_desc* desc, const void* dXhat, const void* 
     g.A = dXhat; g.sAm = d; g.sAk = 1;
     g.B = U; g.sBk = r; g.sBn = 1;
     g.C = q ? (void*)at<float>(ws, Lo.z0) : dZ; g.sCm = r; g.sCn = 1;
-    LAUNCH("dec_bwd:gemm_f32", launch_gemm_f32(g, 0, 0, 0, s));
+    LAUNCH("dec_bwd:gemm_f32", launch_gemm_f32(g, s));
     if (q)
       LAUNCH("dec_bwd_q:rvq_f32", launch_rvq_f32(at<float>(ws, Lo.z0), q->C, (int)T, (int)r, q->L, q->K, q->codes,
                                                  q->code_bytes, s));
@@ -752,15 +751,11 @@ int decode_bwd_impl(const mapl_codec_desc* desc, const void* dXhat, const void* 
     Zh = z;
   }
   if (need_anchor) {
-    float* a = at<float>(ws, Lo.ga);
-    LAUNCH("dec_bwd:gather_rows_f32", launch_gather_rows_f32((const float*)A_r, (int)k, ids, (int)D.V, (int)T, a, s));
     float* z2 = at<float>(ws, Lo.z2);
-    GemmF32Args g = gemm((int)T, (int)r, (int)k);
-    g.A = a; g.sAm = k; g.sAk = 1;
-    g.B = B_r; g.sBk = r; g.sBn = 1;
-    g.Cin = Zh; g.sCinm = r; g.sCinn = 1; g.beta = 1.f;
-    g.C = z2; g.sCm = r; g.sCn = 1;
-    LAUNCH("dec_bwd:gemm_f32", launch_gemm_f32(g, 0, 0, 0, s));
+    GemmF32sArgs g = gemm_s(T, r, z2, r);
+    add_cin(g, Zh, r);
+    add_seg(g, A_r, k, 1, B_r, r, 1, k, 1.f, ids, 1, D.V);
+    LAUNCH("dec_bwd:gemm_f32s", launch_gemm_f32s(g, s));
     Zh = z2;
   }
   {
@@ -769,7 +764,7 @@ int decode_bwd_impl(const mapl_codec_desc* desc, const void* dXhat, const void* 
     g.B = Zh; g.sBk = r; g.sBn = 1;
     if (accumulate_dU) { g.Cin = dU; g.sCinm = r; g.sCinn = 1; g.beta = 1.f; }
     g.C = dU; g.sCm = r; g.sCn = 1;
-    LAUNCH("dec_bwd:gemm_f32", launch_gemm_f32(g, 0, 0, 0, s));
+    LAUNCH("dec_bwd:gemm_f32", launch_gemm_f32(g, s));
   }
   return MAPL_OK;
 }
@@ -925,33 +920,31 @@ extern "C" int mapl_encode_bwd(const mapl_codec_desc* desc, const void* dZ, cons
     g.A = dZ; g.sAm = r; g.sAk = 1;
     g.B = U; g.sBk = 1; g.sBn = r;
     g.C = dX; g.sCm = d; g.sCn = 1;
-    LAUNCH("enc_bwd:gemm_f32", launch_gemm_f32(g, 0, 0, 0, s));
+    LAUNCH("enc_bwd:gemm_f32", launch_gemm_f32(g, s));
   }
-  {
+  // X^T dZ and -B_s^T (a_s^T dZ) in one launch where dU is small, else the
+  // second added to the first
+  float* Wm = need_anchor ? at<float>(ws, Lo.wsum) : nullptr;
+  if (need_anchor) {
+    GemmF32sArgs g = gemm_s(k, r, Wm, r);
+    add_seg(g, A_s, 1, k, dZ, r, 1, T, 1.f, ids, 2, D.V);
+    LAUNCH("enc_bwd:gemm_f32s", launch_gemm_f32s(g, s));
+  }
+  GemmF32sArgs q = gemm_s(d, r, dU, r);
+  if (gemm_f32_small(d, r, 1)) {
+    add_seg(q, X, 1, d, dZ, r, 1, T);
+    if (accumulate_dU) add_cin(q, dU, r);
+  } else {
     GemmF32Args g = gemm((int)d, (int)r, (int)T);
     g.A = X; g.sAm = 1; g.sAk = d;
     g.B = dZ; g.sBk = r; g.sBn = 1;
     if (accumulate_dU) { g.Cin = dU; g.sCinm = r; g.sCinn = 1; g.beta = 1.f; }
     g.C = dU; g.sCm = r; g.sCn = 1;
-    LAUNCH("enc_bwd:gemm_f32", launch_gemm_f32(g, 0, 0, 0, s));
+    LAUNCH("enc_bwd:gemm_f32", launch_gemm_f32(g, s));
+    add_cin(q, dU, r);
   }
-  if (need_anchor) {
-    float* a = at<float>(ws, Lo.ga);
-    float* Wm = at<float>(ws, Lo.wsum);
-    LAUNCH("enc_bwd:gather_rows_f32", launch_gather_rows_f32((const float*)A_s, (int)k, ids, (int)D.V, (int)T, a, s));
-    GemmF32Args g = gemm((int)k, (int)r, (int)T);
-    g.A = a; g.sAm = 1; g.sAk = k;
-    g.B = dZ; g.sBk = r; g.sBn = 1;
-    g.C = Wm; g.sCm = r; g.sCn = 1;
-    LAUNCH("enc_bwd:gemm_f32", launch_gemm_f32(g, 0, 0, 0, s));
-    GemmF32Args e = gemm((int)d, (int)r, (int)k);
-    e.A = B_s; e.sAm = 1; e.sAk = d;
-    e.B = Wm; e.sBk = r; e.sBn = 1;
-    e.Cin = dU; e.sCinm = r; e.sCinn = 1; e.beta = 1.f;
-    e.C = dU; e.sCm = r; e.sCn = 1;
-    e.alpha = -1.f;
-    LAUNCH("enc_bwd:gemm_f32", launch_gemm_f32(e, 0, 0, 0, s));
-  }
+  if (need_anchor) add_seg(q, B_s, 1, d, Wm, r, 1, k, -1.f);
+  if (q.nseg > 0) LAUNCH("enc_bwd:gemm_f32s", launch_gemm_f32s(q, s));
   return MAPL_OK;
 }
 
@@ -1009,7 +1002,7 @@ extern "C" int mapl_stiefel_step(int64_t P, int64_t d, int64_t r, float* U, cons
     g.B = X; g.sBk = r; g.sBn = 1; g.sBb = n;
     g.C = S; g.sCm = r; g.sCn = 1; g.sCb = rr;
     g.sk_part = skp;  // split over two workgroups per CU where the upper tiles are fewer
-    return launch_gemm_f32(g, 0, 0, 0, s);
+    return launch_gemm_f32(g, s);
   };
   // Qo = (a I + b S' + c S' S') / a with S' = sp S (sp: a per-projector
   // factor, or none); symmetric, like every r x r product of the iteration
@@ -1026,7 +1019,7 @@ extern "C" int mapl_stiefel_step(int64_t P, int64_t d, int64_t r, float* U, cons
     g.C = Qo; g.sCm = r; g.sCn = 1; g.sCb = rr;
     g.alpha = (float)(cc / a); g.beta = (float)(b / a); g.diag = 1.f;
     g.beta_ptr = sp;
-    return launch_gemm_f32(g, 0, 0, 0, s);
+    return launch_gemm_f32(g, s);
   };
   // Xo = alpha X' Bm with X' = pre X, or with Yin: Xo = Yin - lr alpha X' Bm
   // (the LMO's last product and Eq. 7's argument U - lr D in one launch)
@@ -1043,7 +1036,7 @@ extern "C" int mapl_stiefel_step(int64_t P, int64_t d, int64_t r, float* U, cons
       g.Cin = Yin; g.sCinm = r; g.sCinn = 1; g.sCinb = n; g.beta = 1.f;
       g.alpha = (float)(-lr * alpha);
     }
-    return launch_gemm_f32(g, 0, 0, 0, s);
+    return launch_gemm_f32(g, s);
   };
   // Co = (A scaled by pre inside) B for r x r factors, fp16 split; sym: the
   // product is symmetric (upper tiles computed, mirrored)
@@ -1057,7 +1050,7 @@ extern "C" int mapl_stiefel_step(int64_t P, int64_t d, int64_t r, float* U, cons
     g.A = Am; g.sAm = r; g.sAk = 1; g.sAb = rr;
     g.B = Bm; g.sBk = r; g.sBn = 1; g.sBb = rr;
     g.C = Co; g.sCm = r; g.sCn = 1; g.sCb = rr;
-    return launch_gemm_f32(g, 0, 0, 0, s);
+    return launch_gemm_f32(g, s);
   };
 
   // C1 = A1 Bm and C2 = A2 Bm in one launch (two symmetric r x r products sharing Bm)
@@ -1070,7 +1063,7 @@ extern "C" int mapl_stiefel_step(int64_t P, int64_t d, int64_t r, float* U, cons
     g.A = A1; g.A2 = A2m; g.sAm = r; g.sAk = 1; g.sAb = rr;
     g.B = Bm; g.sBk = r; g.sBn = 1; g.sBb = rr;
     g.C = C1; g.C2 = C2o; g.sCm = r; g.sCn = 1; g.sCb = rr;
-    return launch_gemm_f32(g, 0, 0, 0, s);
+    return launch_gemm_f32(g, s);
   };
 
   // Eq. 4: S = U^T G, sym, g_R = G - U sym(S)  -> X0
@@ -1080,7 +1073,7 @@ extern "C" int mapl_stiefel_step(int64_t P, int64_t d, int64_t r, float* U, cons
     g.A = U; g.sAm = 1; g.sAk = r; g.sAb = n;
     g.B = G; g.sBk = r; g.sBn = 1; g.sBb = n;
     g.C = S; g.sCm = r; g.sCn = 1; g.sCb = rr;
-    LAUNCH("stiefel:gemm_f32", launch_gemm_f32(g, 0, 0, 0, s));
+    LAUNCH("stiefel:gemm_f32", launch_gemm_f32(g, s));
   }
   LAUNCH("stiefel:symmetrize", launch_symmetrize(S, (int)P, (int)r, s));
   {
@@ -1091,7 +1084,7 @@ extern "C" int mapl_stiefel_step(int64_t P, int64_t d, int64_t r, float* U, cons
     g.Cin = G; g.sCinm = r; g.sCinn = 1; g.sCinb = n; g.beta = 1.f;
     g.C = X0; g.sCm = r; g.sCn = 1; g.sCb = n;
     g.alpha = -1.f;
-    LAUNCH("stiefel:gemm_f32", launch_gemm_f32(g, 0, 0, 0, s));
+    LAUNCH("stiefel:gemm_f32", launch_gemm_f32(g, s));
   }
   // Eq. 5 and the LMO normalisation 1 / (||M||_F + 1e-7); the LMO is 0 for
   // a momentum at or below 2^-20 ||G||_F (under fp32 resolution of G)
@@ -1290,14 +1283,14 @@ extern "C" int mapl_anchor_bwd(const mapl_codec_desc* desc, int side, const void
       e.A = B; e.sAm = d; e.sAk = 1;
       e.B = U; e.sBk = r; e.sBn = 1;
       e.C = BU; e.sCm = r; e.sCn = 1;
-      LAUNCH("anchor_bwd:gemm_f32", launch_gemm_f32(e, 0, 0, 0, s));
+      LAUNCH("anchor_bwd:gemm_f32", launch_gemm_f32(e, s));
       Bk = BU;
     }
     GemmF32Args e = gemm((int)T, (int)k, Lo.K);
     e.A = dY; e.sAm = Lo.K; e.sAk = 1;
     e.B = Bk; e.sBk = 1; e.sBn = Lo.K;
     e.C = g; e.sCm = Lo.kp; e.sCn = 1;
-    LAUNCH("anchor_bwd:gemm_f32", launch_gemm_f32(e, 0, 0, 0, s));
+    LAUNCH("anchor_bwd:gemm_f32", launch_gemm_f32(e, s));
   }
   // 2. tokens sorted by id (stable), 3. per-id sums in sorted order
   const int32_t *skey = nullptr, *sval = nullptr;
