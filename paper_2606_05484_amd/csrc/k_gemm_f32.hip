@@ -1,7 +1,6 @@
 // Batched strided fp32 GEMM:
-//   C[b](m,n) = alpha_b * sum_k A[b](m,k) B[b](k,n) + beta_b * Cin[b](m,n)
-// with alpha_b = alpha * (alpha_ptr ? alpha_ptr[b] : 1), likewise beta, on
-// the fp32 matrix units (v_mfma_f32_32x32x2_f32) or, with GEMM_SPLIT_F16, as
+//   C[b](m,n) = alpha * sum_k A[b](m,k) B[b](k,n) + beta * Cin[b](m,n)
+// on the fp32 matrix units (v_mfma_f32_32x32x2_f32) or, with GEMM_SPLIT_F16, as
 // products of fp16 pieces on the 16-bit matrix units (k_gemm_x3).  Products
 // with few output tiles, or with strides that the vector loads here do not
 // take, run in k_gemm_f32s.hip.
@@ -114,20 +113,15 @@ __device__ __forceinline__ void sk_run(const GemmF32Args& g, F&& products, int t
 
 // The epilogue of the aligned kernels for one wave's 32F x 32F block of
 // tile (tbm, tbn) (tiles of 64F x 64F, 2 x 2 waves): C = alpha acc +
-// beta Cin, plus diag where m == n, and the mirrored element of an
-// off-diagonal tile of a symmetric product.  Cin is
-// read in full before the first store: C may alias Cin as far as the
+// beta Cin, and the mirrored element of an off-diagonal tile of a symmetric
+// product.  Cin is read in full before the first store: C may alias Cin as far as the
 // compiler knows, which would otherwise hold every load behind the store
 // before it.
 template <int F = 2>
 __device__ __forceinline__ void gv_epilogue(const GemmF32Args& g, const f32x16_t (&acc)[F][F], int b, int tbm,
                                             int tbn, int lane, int wm, int wn) {
   const int m0 = (tbm * 2 + wm) * 32 * F, n0 = (tbn * 2 + wn) * 32 * F;
-  const bool second = g.A2 && b >= g.bsplit;  // the second product of a paired launch
-  void* const Cbase = second ? g.C2 : g.C;
-  if (second) b -= g.bsplit;
-  const float alpha = g.alpha * (g.alpha_ptr ? g.alpha_ptr[b] : 1.f);
-  const float beta = g.beta * (g.beta_ptr ? g.beta_ptr[b] : 1.f);
+  const float alpha = g.alpha, beta = g.beta;
   const bool has_cin = g.Cin && beta != 0.f;
   float cin[F][F][16];
   if (has_cin) {
@@ -142,7 +136,7 @@ __device__ __forceinline__ void gv_epilogue(const GemmF32Args& g, const f32x16_t
           cin[i][j][e] = (m < g.M && n < g.N) ? Cin[m * g.sCinm + n * g.sCinn] : 0.f;
         }
   }
-  float* C = (float*)Cbase + b * g.sCb;
+  float* C = (float*)g.C + b * g.sCb;
 #pragma unroll
   for (int i = 0; i < F; ++i)
 #pragma unroll
@@ -153,7 +147,6 @@ __device__ __forceinline__ void gv_epilogue(const GemmF32Args& g, const f32x16_t
         if (m < g.M && n < g.N) {
           float v = alpha * acc[i][j][e];
           if (has_cin) v += beta * cin[i][j][e];
-          if (m == n) v += g.diag;
           C[m * g.sCm + n * g.sCn] = v;
           if (g.sym_upper && tbm != tbn) C[n * g.sCm + m * g.sCn] = v;
         }
@@ -347,13 +340,10 @@ __global__ __launch_bounds__(GF_THREADS) __attribute__((amdgpu_waves_per_eu(256 
   // the products of tile (tbm, tbn) of batch entry b over k-stages [ks0, ks1)
   auto products = [&](int b, int tbm, int tbn, int ks0, int ks1, f32x16_t (&acc)[F][F]) {
   const int m0 = tbm * BT, n0 = tbn * BT;
-  // a paired launch's second product: A2 and entry b - bsplit of the rest
-  const bool second = g.A2 && b >= g.bsplit;
-  const int e = second ? b - g.bsplit : b;
   const __amdgpu_buffer_rsrc_t rA =
-      gv_rsrc((const float*)(second ? g.A2 : g.A) + e * g.sAb,
+      gv_rsrc((const float*)g.A + b * g.sAb,
               (AK ? (int64_t)(g.M - 1) * g.sAm + g.K : (int64_t)(g.K - 1) * g.sAk + g.M) * 4);
-  const __amdgpu_buffer_rsrc_t rB = gv_rsrc((const float*)g.B + e * g.sBb, ((int64_t)(g.K - 1) * g.sBk + g.N) * 4);
+  const __amdgpu_buffer_rsrc_t rB = gv_rsrc((const float*)g.B + b * g.sBb, ((int64_t)(g.K - 1) * g.sBk + g.N) * 4);
   typedef raw4_t raw_t;
   // two register sets: the loads of stages it + 1 and it + 2 are in flight
   // while stage it is multiplied
@@ -379,8 +369,8 @@ __global__ __launch_bounds__(GF_THREADS) __attribute__((amdgpu_waves_per_eu(256 
     }
   };
   // the fp16 split's prescale: 2^8 times the operand's factor for this batch entry
-  const float sa = 256.f * (g.pre_a ? g.pre_a[e] : 1.f);
-  const float sb = 256.f * (g.pre_b ? g.pre_b[e] : 1.f);
+  const float sa = 256.f * (g.pre_a ? g.pre_a[b] : 1.f);
+  const float sb = 256.f * (g.pre_b ? g.pre_b[b] : 1.f);
   // hi and lo pieces of two floats, packed
   auto split2 = [](float x, float y, uint32_t& hi, uint32_t& lo, float sc) {
     const f32x2_t v = (f32x2_t){x, y} * sc;
@@ -522,13 +512,12 @@ __global__ __launch_bounds__(256) void k_gemm_sk_fix(GemmF32Args g) {
   int b, bm, bn;
   sk_tile(t, g.M, b, bm, bn);
   const int mb = bm * GV_BM + wm * 64, nb = bn * GV_BN + wn * 64;
-  const float alpha = g.alpha * (g.alpha_ptr ? g.alpha_ptr[b] : 1.f);
+  const float alpha = g.alpha;
   float* C = (float*)g.C + b * g.sCb;
 #pragma unroll
   for (int e = 0; e < 16; ++e) {
     const int mm = i * 32 + acc_row(e, lane), nn = j * 32 + (lane & 31);
     float x = alpha * v[e];
-    if (mb + mm == nb + nn) x += g.diag;
     if (mb + mm < g.M && nb + nn < g.N) C[(mb + mm) * g.sCm + (nb + nn) * g.sCn] = x;
     L[mm][nn] = x;
   }
@@ -563,8 +552,6 @@ hipError_t launch_gemm_f32(const GemmF32Args& g, hipStream_t s) {
   if (g.sk_part && g.Cin) return hipErrorInvalidValue;  // the fix-up applies no Cin
   if (g.split < 0 || g.split > GEMM_SPLIT_F16) return hipErrorInvalidValue;
   if ((g.pre_a || g.pre_b) && g.split != GEMM_SPLIT_F16) return hipErrorInvalidValue;
-  if (g.A2 && (g.split != GEMM_SPLIT_F16 || !g.C2 || g.sk_part || g.bsplit <= 0 || g.bsplit >= g.batch))
-    return hipErrorInvalidValue;
   if (g.sk_part && !g.sym_upper) return hipErrorInvalidValue;
   const int ntm = (g.M + GV_BM - 1) / GV_BM;
   const dim3 vgrid = g.sk_part      ? dim3(gemm_f32_sk_plan(g.M, g.K, g.batch).nwg)
@@ -576,6 +563,22 @@ hipError_t launch_gemm_f32(const GemmF32Args& g, hipStream_t s) {
     return hipGetLastError();
   };
   if (g.split && vm < 0) return hipErrorInvalidValue;
+  // Few tiles (a launch bound by one workgroup's walk over K), or strides the
+  // vector loads do not take.  A split Gram product goes there too while its
+  // stream-K fix-up, which sums up to K / 32 pieces per tile in turn, costs
+  // more than the fp32 units' lower rate: [1024, 256] x 3: 26 -> 12 us.
+  const int64_t tiles = (int64_t)ntm * ((g.N + GV_BN - 1) / GV_BN) * g.batch;
+  if (vm < 0 || (g.split ? g.sk_part && tiles < 48 : gemm_f32_small(g.M, g.N, g.batch))) {
+    GemmF32sArgs q{};
+    q.nseg = 1;
+    q.seg[0] = {(const float*)g.A, g.sAm, g.sAk, (const float*)g.B, g.sBk, g.sBn, g.K, nullptr, 0, 0, 1.f};
+    q.M = g.M; q.N = g.N; q.batch = g.batch; q.sAb = g.sAb; q.sBb = g.sBb;
+    q.Cin = g.beta != 0.f ? g.Cin : nullptr; q.sCinm = g.sCinm; q.sCinn = g.sCinn; q.sCinb = g.sCinb;
+    q.C = (float*)g.C; q.sCm = g.sCm; q.sCn = g.sCn; q.sCb = g.sCb;
+    q.alpha = g.alpha; q.beta = g.beta; q.sym_upper = g.sym_upper;
+    q.pre_a = g.pre_a; q.pre_b = g.pre_b;
+    return launch_gemm_f32s(q, s);
+  }
   if (g.split == GEMM_SPLIT_F16) {
     // 64 x 64 tiles where 128 x 128 ones would give fewer than X3_SMALL_BELOW
     // workgroups: such launches are bound by one workgroup's latency, and
@@ -594,19 +597,6 @@ hipError_t launch_gemm_f32(const GemmF32Args& g, hipStream_t s) {
     else hipLaunchKernelGGL((k_gemm_x3<false, GV_BM>), vgrid, dim3(GF_THREADS), 0, s, g);
     const hipError_t e = hipGetLastError();
     return e != hipSuccess ? e : sk_fix();
-  }
-  // few tiles (a launch bound by one workgroup's walk over K), or strides the
-  // vector loads do not take
-  if (vm < 0 || gemm_f32_small(g.M, g.N, g.batch)) {
-    if (g.alpha_ptr || g.beta_ptr) return hipErrorInvalidValue;
-    GemmF32sArgs q{};
-    q.nseg = 1;
-    q.seg[0] = {(const float*)g.A, g.sAm, g.sAk, (const float*)g.B, g.sBk, g.sBn, g.K, nullptr, 0, 0, 1.f};
-    q.M = g.M; q.N = g.N; q.batch = g.batch; q.sAb = g.sAb; q.sBb = g.sBb;
-    q.Cin = g.beta != 0.f ? g.Cin : nullptr; q.sCinm = g.sCinm; q.sCinn = g.sCinn; q.sCinb = g.sCinb;
-    q.C = (float*)g.C; q.sCm = g.sCm; q.sCn = g.sCn; q.sCb = g.sCb;
-    q.alpha = g.alpha; q.beta = g.beta; q.diag = g.diag; q.sym_upper = g.sym_upper;
-    return launch_gemm_f32s(q, s);
   }
   if (vm) hipLaunchKernelGGL(k_gemm_f32v<true>, vgrid, dim3(GF_THREADS), 0, s, g);
   else hipLaunchKernelGGL(k_gemm_f32v<false>, vgrid, dim3(GF_THREADS), 0, s, g);

@@ -148,9 +148,12 @@ __global__ __launch_bounds__(64 * W) void k_gemm_f32s(GemmF32sArgs g) {
       }
     }
   };
+  // A is scaled as it enters, B through the result: nothing leaves fp32's range
+  // where the scaled operands do not
+  const float pa = g.pre_a ? g.pre_a[b] : 1.f, alpha = g.alpha * (g.pre_b ? g.pre_b[b] : 1.f);
   f32x16_t acc = f32x16_t{};
   auto mul = [&](int kb, const FsBatch& x) {
-    const float sg = g.seg[kb >= nb0 ? 1 : 0].sign;
+    const float sg = g.seg[kb >= nb0 ? 1 : 0].sign * pa;
 #pragma unroll
     for (int e = 0; e < 16; ++e) acc = mfma32x32x2f32(sg * x.a[e], x.b[e], acc);
   };
@@ -175,8 +178,7 @@ __global__ __launch_bounds__(64 * W) void k_gemm_f32s(GemmF32sArgs g) {
 #pragma unroll
     for (int w = 1; w < W; ++w) v += part[w][e * 64 + lane];
     const int om = m0 + acc_row(e, lane);
-    v = g.alpha * v + g.beta * cin[q];
-    if (om == n) v += g.diag;
+    v = alpha * v + g.beta * cin[q];
     if (om < g.M && nok) {
       C[om * g.sCm + n * g.sCn] = v;
       if (g.sym_upper && bm != bn) C[n * g.sCm + om * g.sCn] = v;

@@ -34,7 +34,7 @@ hipError_t launch_gemm_tn(const TnArgs& g, hipStream_t s);
 bool gemm_tn_gathers(const TnArgs& g);
 
 // ---------------------------------------------------------------- fp32 GEMM
-// C[b](m,n) = alpha_b sum_k A[b](m,k) B[b](k,n) + beta_b Cin[b](m,n), all fp32; Cin may be null.
+// C[b](m,n) = alpha sum_k A[b](m,k) B[b](k,n) + beta Cin[b](m,n), all fp32; Cin may be null.
 enum { GEMM_SPLIT_NONE = 0, GEMM_SPLIT_F16 = 1 };
 struct GemmF32Args {
   const void* A; int64_t sAm, sAk, sAb;
@@ -43,16 +43,10 @@ struct GemmF32Args {
   void* C; int64_t sCm, sCn, sCb;
   int M, N, K, batch;
   float alpha, beta;
-  const float* alpha_ptr; const float* beta_ptr;
-  float diag;  // added to every element with m == n after the scaling
   int split;  // aligned operands: GEMM_SPLIT_F16 takes the products as
              // hi.hi + hi.lo + lo.hi of fp16 pieces of 2^8 x (|operands| < 255)
   const float* pre_a; const float* pre_b;  // GEMM_SPLIT_F16 only: per-batch factors of A and B
                                            // (null: 1), applied before the split
-  const void* A2; void* C2; int bsplit;   // GEMM_SPLIT_F16 only, optional: batch entries b >= bsplit
-                                           // multiply A2 and write C2 (their entry b - bsplit), with
-                                           // B, Cin and the per-batch factors of entry b - bsplit: two
-                                           // products that share B in one launch
   int sym_upper;   // C = A B known symmetric (M == N; Cin, if any, symmetric too): only tiles on or
                    // above the diagonal are computed, each off-diagonal one also written mirrored
                    // (aligned case)
@@ -80,7 +74,8 @@ struct GemmF32sArgs {
   int M, N, batch; int64_t sAb, sBb;
   const float* Cin; int64_t sCinm, sCinn, sCinb;
   float* C; int64_t sCm, sCn, sCb;
-  float alpha, beta, diag;
+  float alpha, beta;
+  const float* pre_a; const float* pre_b;  // per-batch factors of A and B (null: 1)
   int sym_upper;
 };
 // Whether launch_gemm_f32s is the better kernel for an M x N x batch output.
@@ -266,10 +261,41 @@ hipError_t launch_momentum(float* M, const float* gR, const float* G, int64_t n,
 // (norms from launch_momentum's partials).
 hipError_t launch_fro_scale(const float* partial, int nblk, int P, float eps, float zero_rel, float* scale,
                             hipStream_t s);
-// For S [P][r][r]: nu2 = max_i sum_j |S_ij|; inv_nu = 1/sqrt(nu2), inv_nu2 = 1/nu2;
-// part: P * ceil(r / 16) floats of scratch.
-hipError_t launch_inf_norm_scales(const float* S, int P, int r, float* part, float* inv_nu, float* inv_nu2,
-                                  hipStream_t s);
+// For S [P][r][r]: part[p][q] = max over rows 16 q .. 16 q + 15 of sum_j |S_ij|,
+// q < ceil(r / 16).
+hipError_t launch_inf_norm_partial(const float* S, int P, int r, float* part, hipStream_t s);
+
+// ---------------------------------------------------------------- symmetric r x r products
+// C = alpha A B + beta Cin + diag I for symmetric, commuting matrices held as
+// fp16 planes in matrix-unit order (see k_sym.hip): [P][hi plane, lo plane],
+// r r halves each, of 2^8 x (|x| < 255).  Matrix b of the batch; with A2 and
+// batch == 2 P, entries P .. 2 P - 1 multiply A2 into C2 with the same B.
+// Cin (fp32 [P][r][r], read on and above the diagonal tiles; beta is scaled
+// by beta_ptr[b] if given) may be null.  C (planes) and Cf (fp32; cf_full:
+// all of it, else the tiles on and above the diagonal) may each be null.
+struct SymArgs {
+  const uint16_t* A; const uint16_t* B; const uint16_t* A2;
+  uint16_t* C; uint16_t* C2;
+  const float* Cin; const float* beta_ptr; float* Cf; int cf_full;
+  int r, P, batch;
+  float alpha, beta, diag;
+};
+hipError_t launch_sym(const SymArgs& g, hipStream_t s);
+// Planes of S [P][r][r] (fp32, |x| < 255), or with part (launch_inf_norm_partial)
+// of S / nu^2, nu^2 the largest row sum of |S|; then inv_nu = 1 / nu and
+// inv_nu2 = 1 / nu^2 are written too.
+hipError_t launch_sym_split(const float* S, int P, int r, const float* part, uint16_t* C, float* inv_nu,
+                            float* inv_nu2, hipStream_t s);
+
+// One PolarExpress segment of r <= 64 in one launch: from S [P][r][r] (fp32,
+// with part divided by nu^2 as launch_sym_split does), per step k Q = I + b S
+// + c S S, P <- P Q (from I), S <- a2 Q (S Q); S is replaced by P.
+struct PolarSmallArgs {
+  float* S; int P, r, steps;
+  const float* part; int npart; float* inv_nu;
+  float b[16], c[16], a2[16];
+};
+hipError_t launch_polar_small(const PolarSmallArgs& g, hipStream_t s);
 
 // ---------------------------------------------------------------- codebook synchronisation
 // buf[l][i][:] = C[l][rows[l*n + i]][:] (zeros for rows outside [0, K)); r % 4 == 0.

@@ -1004,23 +1004,6 @@ extern "C" int mapl_stiefel_step(int64_t P, int64_t d, int64_t r, float* U, cons
     g.sk_part = skp;  // split over two workgroups per CU where the upper tiles are fewer
     return launch_gemm_f32(g, s);
   };
-  // Qo = (a I + b S' + c S' S') / a with S' = sp S (sp: a per-projector
-  // factor, or none); symmetric, like every r x r product of the iteration
-  // below
-  auto poly = [&](double a, double b, double cc, const float* sp, float* Qo) {
-    GemmF32Args g = gemm((int)r, (int)r, (int)r);
-    g.split = GEMM_SPLIT_F16;
-    g.sym_upper = 1;
-    g.pre_a = g.pre_b = sp;
-    g.batch = (int)P;
-    g.A = S; g.sAm = r; g.sAk = 1; g.sAb = rr;
-    g.B = S; g.sBk = r; g.sBn = 1; g.sBb = rr;
-    g.Cin = S; g.sCinm = r; g.sCinn = 1; g.sCinb = rr;
-    g.C = Qo; g.sCm = r; g.sCn = 1; g.sCb = rr;
-    g.alpha = (float)(cc / a); g.beta = (float)(b / a); g.diag = 1.f;
-    g.beta_ptr = sp;
-    return launch_gemm_f32(g, s);
-  };
   // Xo = alpha X' Bm with X' = pre X, or with Yin: Xo = Yin - lr alpha X' Bm
   // (the LMO's last product and Eq. 7's argument U - lr D in one launch)
   auto apply = [&](const float* X, const float* pre, const float* Bm, float* Xo, const float* Yin, double alpha) {
@@ -1038,32 +1021,13 @@ extern "C" int mapl_stiefel_step(int64_t P, int64_t d, int64_t r, float* U, cons
     }
     return launch_gemm_f32(g, s);
   };
-  // Co = (A scaled by pre inside) B for r x r factors, fp16 split; sym: the
-  // product is symmetric (upper tiles computed, mirrored)
-  auto rmul = [&](float* Co, const float* Am, const float* Bm, const float* pre, bool sym, double alpha = 1.0) {
-    GemmF32Args g = gemm((int)r, (int)r, (int)r);
-    g.split = GEMM_SPLIT_F16;
+  // r x r products of the iteration: symmetric, in fp16 planes
+  auto sym = [&](uint16_t* C, const uint16_t* A, const uint16_t* B, double alpha) {
+    SymArgs g{};
+    g.A = A; g.B = B; g.C = C;
+    g.r = (int)r; g.P = g.batch = (int)P;
     g.alpha = (float)alpha;
-    g.pre_a = pre;
-    g.sym_upper = sym ? 1 : 0;
-    g.batch = (int)P;
-    g.A = Am; g.sAm = r; g.sAk = 1; g.sAb = rr;
-    g.B = Bm; g.sBk = r; g.sBn = 1; g.sBb = rr;
-    g.C = Co; g.sCm = r; g.sCn = 1; g.sCb = rr;
-    return launch_gemm_f32(g, s);
-  };
-
-  // C1 = A1 Bm and C2 = A2 Bm in one launch (two symmetric r x r products sharing Bm)
-  auto rmul2 = [&](float* C1, const float* A1, float* C2o, const float* A2m, const float* Bm) {
-    GemmF32Args g = gemm((int)r, (int)r, (int)r);
-    g.split = GEMM_SPLIT_F16;
-    g.sym_upper = 1;
-    g.batch = 2 * (int)P;
-    g.bsplit = (int)P;
-    g.A = A1; g.A2 = A2m; g.sAm = r; g.sAk = 1; g.sAb = rr;
-    g.B = Bm; g.sBk = r; g.sBn = 1; g.sBb = rr;
-    g.C = C1; g.C2 = C2o; g.sCm = r; g.sCn = 1; g.sCb = rr;
-    return launch_gemm_f32(g, s);
+    return g;
   };
 
   // Eq. 4: S = U^T G, sym, g_R = G - U sym(S)  -> X0
@@ -1110,14 +1074,14 @@ extern "C" int mapl_stiefel_step(int64_t P, int64_t d, int64_t r, float* U, cons
   // fp16 split's full-precision range; the paper's schedules, 5 and 7
   // steps, are one segment each: 1043 and 116); a longer schedule forms
   // X_j = X_i P_j at a segment's end and starts the next from X_j's Gram
-  // product.  On entry S holds X_0^T X_0 divided by spre (the first step's
-  // products scale it by spre inside, null: 1); X_0 is Xs scaled by xpre
-  // inside its one product.  X_K, or Yin - lr X_K, goes to out (null: the X
+  // product.  On entry S holds X_0^T X_0, or with norm that times nu^2, whose
+  // row sums are in partial; X_0 is Xs scaled by xpre inside its one product.  X_K, or Yin - lr X_K, goes to out (null: the X
   // buffer not read last), and *written names the buffer.
   constexpr double kSegGrowth = 2048.0;
   float* bufs[2] = {X0, X1};
   auto other = [&](const float* p) { return p == bufs[0] ? bufs[1] : bufs[0]; };
-  auto polar_rr = [&](const double (*coef)[3], int steps, const float* Xs, const float* xpre, const float* spre,
+  auto planes = [](float* p) { return (uint16_t*)p; };
+  auto polar_rr = [&](const double (*coef)[3], int steps, const float* Xs, const float* xpre, bool norm,
                       float* out, const float* Yin, float** written) -> int {
     const float* Xseg = Xs;
     for (int i = 0; i < steps;) {
@@ -1125,34 +1089,63 @@ extern "C" int mapl_stiefel_step(int64_t P, int64_t d, int64_t r, float* U, cons
       double growth = 1.0;
       for (; j < steps && (j == i || growth * coef[j][0] <= kSegGrowth); ++j) growth *= coef[j][0];
       if (i > 0) LAUNCH("stiefel:pe_gram", gram(Xseg, GEMM_SPLIT_F16, nullptr));  // S_i = X_i^T X_i
-      const float* Pprev = nullptr;
-      int pq = 0;
-      for (int k = i; k < j; ++k) {
-        const double a = coef[k][0], b = coef[k][1], cc = coef[k][2];
-        const float* sp = k == 0 ? spre : nullptr;
-        float* Q = (k & 1) ? Q2 : Qm;
-        LAUNCH("stiefel:pe_poly", poly(a, b, cc, sp, Q));  // Q~_k
-        const bool pprod = k > i, supd = k + 1 < j;  // P~ <- P~ Q~_k; S_{k+1} = a^2 Q~_k (S_k Q~_k)
-        // S_k, Q~_k and P~ are polynomials in the segment's first S, so they
-        // commute and every product here is symmetric: each computes the
-        // tiles on and above the diagonal and mirrors them
-        if (pprod && supd)  // S_k Q~_k and P~ Q~_k share Q~_k: one launch (sp is null past step 0)
-          LAUNCH("stiefel:pe_sq_p", rmul2(Tm, S, Pq[pq], Pprev, Q));
-        else if (pprod)
-          LAUNCH("stiefel:pe_p", rmul(Pq[pq], Pprev, Q, nullptr, true));
-        else if (supd)
-          LAUNCH("stiefel:pe_sq", rmul(Tm, S, Q, sp, true));
-        if (pprod) {
-          Pprev = Pq[pq];
-          pq ^= 1;
-        } else {
-          Pprev = Q;  // P~ = Q~_i
+      const bool nrm = norm && i == 0;
+      if (r <= 64) {
+        PolarSmallArgs g{};
+        g.S = S; g.P = (int)P; g.r = (int)r; g.steps = j - i;
+        if (nrm) { g.part = partial; g.npart = (int)((r + 15) / 16); g.inv_nu = inv_nu; }
+        for (int k = i; k < j; ++k) {
+          g.b[k - i] = (float)(coef[k][1] / coef[k][0]);
+          g.c[k - i] = (float)(coef[k][2] / coef[k][0]);
+          g.a2[k - i] = (float)(coef[k][0] * coef[k][0]);
         }
-        if (supd) LAUNCH("stiefel:pe_s", rmul(S, Q, Tm, nullptr, true, a * a));  // S_{k+1} (symmetric)
+        LAUNCH("stiefel:pe_small", launch_polar_small(g, s));
+      } else {
+        // the segment's S in planes (in the X buffer that its end overwrites);
+        // S itself keeps the fp32 values that the polynomials' linear term takes
+        uint16_t* Sp = planes(other(Xseg));
+        LAUNCH("stiefel:pe_split", launch_sym_split(S, (int)P, (int)r, nrm ? partial : nullptr, Sp, inv_nu, inv_nu2, s));
+        const uint16_t* Pprev = nullptr;
+        int pq = 0;
+        for (int k = i; k < j; ++k) {
+          const double a = coef[k][0], b = coef[k][1], cc = coef[k][2];
+          uint16_t* Q = planes((k & 1) ? Q2 : Qm);
+          const bool pprod = k > i, supd = k + 1 < j;  // P~ <- P~ Q~_k; S_{k+1} = a^2 Q~_k (S_k Q~_k)
+          {
+            // Q~_k = (a I + b S + c S S) / a
+            SymArgs g = sym(Q, Sp, Sp, cc / a);
+            g.Cin = S; g.beta = (float)(b / a); g.diag = 1.f;
+            g.beta_ptr = nrm && k == i ? inv_nu2 : nullptr;
+            if (j == i + 1) { g.Cf = S; g.cf_full = 1; }  // a single step: Q~ is P~
+            LAUNCH("stiefel:pe_poly", launch_sym(g, s));
+          }
+          if (pprod && supd) {  // S_k Q~_k and P~ Q~_k share Q~_k: one launch
+            SymArgs g = sym(planes(Tm), Sp, Q, 1.0);
+            g.A2 = Pprev; g.C2 = planes(Pq[pq]); g.batch = 2 * (int)P;
+            LAUNCH("stiefel:pe_sq_p", launch_sym(g, s));
+          } else if (pprod) {  // the segment's last: P~ in fp32 for the product that forms X
+            SymArgs g = sym(nullptr, Pprev, Q, 1.0);
+            g.Cf = S; g.cf_full = 1;
+            LAUNCH("stiefel:pe_p", launch_sym(g, s));
+          } else if (supd) {
+            LAUNCH("stiefel:pe_sq", launch_sym(sym(planes(Tm), Sp, Q, 1.0), s));
+          }
+          if (pprod) {
+            Pprev = planes(Pq[pq]);
+            pq ^= 1;
+          } else {
+            Pprev = Q;  // P~ = Q~_i
+          }
+          if (supd) {  // S_{k+1}
+            SymArgs g = sym(Sp, Q, planes(Tm), a * a);
+            g.Cf = S;
+            LAUNCH("stiefel:pe_s", launch_sym(g, s));
+          }
+        }
       }
       float* Xo = j == steps && out ? out : other(Xseg);
       LAUNCH("stiefel:pe_apply",
-             apply(Xseg, i == 0 ? xpre : nullptr, Pprev, Xo, j == steps ? Yin : nullptr, growth));
+             apply(Xseg, i == 0 ? xpre : nullptr, S, Xo, j == steps ? Yin : nullptr, growth));
       Xseg = Xo;
       i = j;
     }
@@ -1164,12 +1157,12 @@ extern "C" int mapl_stiefel_step(int64_t P, int64_t d, int64_t r, float* U, cons
   // (D itself is not kept)
   LAUNCH("stiefel:lmo_gram", gram(M, GEMM_SPLIT_F16, scale));
   float* Y = nullptr;
-  if ((st = polar_rr(kLmoCoef, lmo_steps, M, scale, nullptr, nullptr, U, &Y))) return st;
+  if ((st = polar_rr(kLmoCoef, lmo_steps, M, scale, false, nullptr, U, &Y))) return st;
   // Eq. 7: U = PE(Y / nu), nu^2 = max row sum |Y^T Y|: Y^T Y in fp32 (it fixes nu)
   LAUNCH("stiefel:gram", gram(Y, GEMM_SPLIT_NONE, nullptr));
   // (the momentum's norm partials are consumed by now; their buffer takes the row maxima)
-  LAUNCH("stiefel:inf_norm_scales", launch_inf_norm_scales(S, (int)P, (int)r, partial, inv_nu, inv_nu2, s));
-  if ((st = polar_rr(kRetractCoef, retract_steps, Y, inv_nu, inv_nu2, U, nullptr, nullptr))) return st;
+  LAUNCH("stiefel:inf_norm", launch_inf_norm_partial(S, (int)P, (int)r, partial, s));
+  if ((st = polar_rr(kRetractCoef, retract_steps, Y, inv_nu, true, U, nullptr, nullptr))) return st;
   return MAPL_OK;
 }
 
