@@ -6,13 +6,11 @@
 // sum gathers anchor rows T[ids[t]] (bf16, [V, ldt]) -- the token-id lookup of
 // Eqs. 1-2 -- straight into the K loop, so the anchored operand [X | a] is
 // never materialised.  fp32 accumulation; the epilogue stores bf16 (RNE) or
-// fp32 (optionally accumulating).  One kernel serves the dense products of
-// the codec:
+// fp32.  One kernel serves the dense products of the codec:
 //   encode      Z0   = [X | a_s] [U~ ; -(B_s U~)]        (N = r)
 //   decode_bwd  dZ   = dXhat U~                          (N = r)
 //   decode      Xhat = [Zhat | a_r] [U~^T ; B_r]         (N = d)
 //   encode_bwd  dX   = dZ U~^T                           (N = d)
-// and, with split-K over grid z, the small per-call operand products.
 //
 // Pipeline: a workgroup of 4 waves owns BM = 128 tokens and walks a run of
 // BN-wide output tiles; K is staged 64 at a time through three LDS stages
@@ -27,8 +25,12 @@
 // operand and the tokens as the second, so each lane ends up holding four
 // consecutive output columns of one token: fp32 results leave as 16 B
 // stores, bf16 results are paired across lane halves (v_permlane32_swap) into
-// 16 B row segments and staged through LDS into full 128 B row writes.  Buffer resources bound every
-// operand: lanes past the last token row, past Kg or past ldw read zeros.
+// 16 B row segments and staged through LDS into full 128 B row writes.  Buffer
+// resources bound every operand: lanes past the last token row or past Kg
+// read zeros.  A gathered width that ends inside a stage costs one selection
+// per load of that stage (kept as per-load tables in the step plan it went
+// through scratch memory: T = 32768, K = 2048 + 48: 144 -> 39 us; the
+// short-K kernel with K = 128 + 48 in place of this one: 107 -> 35 us).
 #include "tn_gemm.hpp"
 #include "short_plan.hpp"
 
@@ -47,7 +49,7 @@ __global__ __launch_bounds__(GTHREADS) void k_gemm_tn(TnArgs g, int ntiles_per_w
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int m0 = blockIdx.x * GM, nt0 = blockIdx.y * ntiles_per_wg;
-  char* obase = (char*)g.out + (g.kz > 0 ? (int64_t)blockIdx.z * g.out_z * 4 : 0);
+  char* obase = (char*)g.out;
   tn_mainloop<BN, NS, FULLK>(g, ntiles_per_wg, S0.a, S0.w, S1.a, S1.w, S2buf, S2buf + GM * GK,
                              [&](f32x16_t (&acc)[2][BN / 64], int tile) {
                                // epilogue, staging bf16 results through the buffer consumed by the
@@ -86,7 +88,7 @@ __global__ __launch_bounds__(GTHREADS) void k_gemm_tn(TnArgs g, int ntiles_per_w
 // stage wait is a fixed vmcnt count, computed below from that order.
 constexpr int SH_BM = 256, SH_BN = 128;
 
-template <int KS>
+template <int KS, bool PART>
 __global__ __launch_bounds__(GTHREADS, 1) void k_gemm_tn_short(TnArgs g, int ntiles_per_wg) {
 #if defined(__HIP_DEVICE_COMPILE__)
   using P = ShortPlan<KS>;
@@ -127,7 +129,8 @@ __global__ __launch_bounds__(GTHREADS, 1) void k_gemm_tn_short(TnArgs g, int nti
       for (int q = 0; q < KST; ++q) {
         const int kc = q * 16;
         const bool in_a = kc < g.Ka;
-        afr[i][q] = __builtin_amdgcn_raw_buffer_load_b128(in_a ? ra : rt, in_a ? aoff : toff,
+        const bool none = PART && kc >= g.Ka + g.Kg;  // past the gathered width
+        afr[i][q] = __builtin_amdgcn_raw_buffer_load_b128(in_a ? ra : rt, none ? OOB : in_a ? aoff : toff,
                                                           in_a ? kc * 2 : (kc - g.Ka) * 2, 0);
       }
     }
@@ -174,7 +177,8 @@ __global__ __launch_bounds__(GTHREADS, 1) void k_gemm_tn_short(TnArgs g, int nti
           }
           afr[i][q] = u32x4{pack_bf2(v[0], v[1]), pack_bf2(v[2], v[3]), pack_bf2(v[4], v[5]), pack_bf2(v[6], v[7])};
         } else {
-          afr[i][q] = __builtin_amdgcn_raw_buffer_load_b128(rt, toff, (kc - g.Ka) * 2, 0);
+          const bool none = PART && kc >= g.Ka + g.Kg;
+          afr[i][q] = __builtin_amdgcn_raw_buffer_load_b128(rt, none ? OOB : toff, (kc - g.Ka) * 2, 0);
         }
       }
     }
@@ -183,7 +187,10 @@ __global__ __launch_bounds__(GTHREADS, 1) void k_gemm_tn_short(TnArgs g, int nti
   // W stage s (tile s / KS, k 64 (s % KS) ..) goes to ring slot s % NSW as
   // 128 B rows, 16 B chunks swizzled by ((row >> 1) & 7); block j of a wave
   // covers rows 8 (4 wave + j) .. +7
+  // (PART: the gathered width ends inside the last stage; chunks past it read
+  // zeros, per block parity)
   uint32_t w_off[WBLK];
+  bool w_ok[2] = {true, true};
   {
     const int lrow = lane >> 3;
     const uint32_t lchp[2] = {(uint32_t)((lane & 7) ^ (lane >> 4)), (uint32_t)((lane & 7) ^ (4 + (lane >> 4)))};
@@ -192,13 +199,16 @@ __global__ __launch_bounds__(GTHREADS, 1) void k_gemm_tn_short(TnArgs g, int nti
       const int row = 8 * (wave * WBLK + j) + lrow;
       w_off[j] = (uint32_t)row * (uint32_t)g.ldw * 2u + 16u * lchp[j & 1];
     }
+    if (PART)
+#pragma unroll
+      for (int h = 0; h < 2; ++h) w_ok[h] = (KS - 1) * GK + 8 * (int)lchp[h] < g.Ka + g.Kg;
   }
   const uint32_t ntile_bytes = (uint32_t)BN * (uint32_t)g.ldw * 2u;
   // the DMA cursor: the stage it fills next, its ring slot, its byte offset in W
   int d_stage = 0, d_slot = 0, d_ks = 0;
   uint32_t d_off = (uint32_t)nt0 * ntile_bytes;
   auto dma_block = [&](int j) {
-    const bool live = d_stage < total;
+    const bool live = d_stage < total && (!PART || d_ks + 1 < KS || w_ok[j & 1]);
     bf16_t* dst = SW + d_slot * (BN * GK) + (wave * WBLK + j) * 512;
     __builtin_amdgcn_raw_ptr_buffer_load_lds(rw, (lds_ptr)dst, 16, live ? w_off[j] : OOB, (int)d_off, 0, 0);
   };
@@ -356,15 +366,13 @@ __global__ __launch_bounds__(GTHREADS, 1) void k_gemm_tn_short(TnArgs g, int nti
 
 template <int BN, int NS>
 hipError_t launch_bn(const TnArgs& g, hipStream_t s) {
-  const int kz = g.kz > 0 ? g.kz : g.Ka;
-  const bool fullk = kz % GK == 0 && g.Kg % GK == 0 && g.Ka + g.Kg <= g.ldw;
+  const bool fullk = g.Kg % GK == 0;
   const int mt = (g.M + GM - 1) / GM;
   const int nt = g.N / BN;
-  const int zs = g.kz > 0 ? g.Ka / g.kz : 1;
   // enough workgroups to cover the chip once; each walks a run of N tiles
   int per = 1;
-  while (per < nt && (int64_t)mt * ((nt + per * 2 - 1) / (per * 2)) * zs >= 256) per *= 2;
-  dim3 grid(mt, (nt + per - 1) / per, zs);
+  while (per < nt && (int64_t)mt * ((nt + per * 2 - 1) / (per * 2)) >= 256) per *= 2;
+  dim3 grid(mt, (nt + per - 1) / per);
   if (fullk)
     hipLaunchKernelGGL((k_gemm_tn<BN, NS, true>), grid, dim3(GTHREADS), 0, s, g, per);
   else
@@ -376,8 +384,7 @@ template <int BN>
 hipError_t launch_ns(const TnArgs& g, hipStream_t s) {
   // Three stages, unless a short K would pad its step count (a multiple of
   // the stage count) by a large fraction: then two.
-  const int kz = g.kz > 0 ? g.kz : g.Ka;
-  const int KS = (kz + GK - 1) / GK + (g.Kg + GK - 1) / GK;
+  const int KS = g.Ka / GK + (g.Kg + GK - 1) / GK;
   if (KS % 3 != 0 && KS < 24 && KS % 2 == 0) return launch_bn<BN, 2>(g, s);
   return launch_bn<BN, 3>(g, s);
 }
@@ -385,13 +392,11 @@ hipError_t launch_ns(const TnArgs& g, hipStream_t s) {
 }  // namespace
 
 // Tiles per workgroup of the short-K kernel for g, or 0 where it does not
-// apply: bf16 output, 2 to 6 full stages, N a multiple of 128, and at least
+// apply: bf16 output, 2 to 6 stages, N a multiple of 128, and at least
 // two tiles per workgroup with one 256-token workgroup per CU.
 static int short_per(const TnArgs& g) {
-  const int ks = (g.Ka + g.Kg) / GK;
-  if (g.M <= 0 || g.out_f32 || g.kz != 0 || g.Ka % GK || g.Kg % GK || g.Ka + g.Kg > g.ldw || g.N % SH_BN ||
-      ks < 2 || ks > 6)
-    return 0;
+  const int ks = (g.Ka + g.Kg + GK - 1) / GK;
+  if (g.M <= 0 || g.out_f32 || g.N % SH_BN || ks < 2 || ks > 6) return 0;
   if (g.codes && (g.L < 1 || g.L > 2 || !g.C || g.K < 1 || (g.code_bytes != 1 && g.code_bytes != 2))) return 0;
   const int mt = (g.M + SH_BM - 1) / SH_BM, nt = g.N / SH_BN;
   int per = 1;
@@ -403,27 +408,40 @@ bool gemm_tn_gathers(const TnArgs& g) { return short_per(g) >= 2; }
 
 hipError_t launch_gemm_tn(const TnArgs& g, hipStream_t s) {
   if (g.M <= 0) return hipSuccess;
-  if (g.kz > 0 && (g.kz % GK != 0 || g.Ka % g.kz != 0 || g.Kg != 0)) return hipErrorInvalidValue;
-  const int per = short_per(g);
-  if (g.codes && per < 2) return hipErrorInvalidValue;
+  if (g.Ka % GK || g.Kg % 16 || g.N % 64 || g.Ka + g.Kg > g.ldw) return hipErrorInvalidValue;
   // a short K (2 to 6 stages) walked over several 128-column tiles with bf16
   // output (decode, encode_bwd): one 256-token workgroup per CU, each walking
   // per tiles, as long as every workgroup gets at least two
-  {
-    const int ks = (g.Ka + g.Kg) / GK;
-    if (per >= 2) {
-      const int mt = (g.M + SH_BM - 1) / SH_BM, nt = g.N / SH_BN;
-      const dim3 grid(mt, (nt + per - 1) / per);
-      switch (ks) {
-        case 2: hipLaunchKernelGGL((k_gemm_tn_short<2>), grid, dim3(GTHREADS), 0, s, g, per); break;
-        case 3: hipLaunchKernelGGL((k_gemm_tn_short<3>), grid, dim3(GTHREADS), 0, s, g, per); break;
-        case 4: hipLaunchKernelGGL((k_gemm_tn_short<4>), grid, dim3(GTHREADS), 0, s, g, per); break;
-        case 5: hipLaunchKernelGGL((k_gemm_tn_short<5>), grid, dim3(GTHREADS), 0, s, g, per); break;
-        default: hipLaunchKernelGGL((k_gemm_tn_short<6>), grid, dim3(GTHREADS), 0, s, g, per); break;
-      }
-      return hipGetLastError();
+  const int per = short_per(g);
+  if (g.codes && per < 2) return hipErrorInvalidValue;
+  if (per >= 2) {
+    const int ks = (g.Ka + g.Kg + GK - 1) / GK;
+    const int mt = (g.M + SH_BM - 1) / SH_BM, nt = g.N / SH_BN;
+    const dim3 grid(mt, (nt + per - 1) / per);
+    const bool part = g.Kg % GK != 0;
+#define MAPL_SHORT(KS_)                                                                                       \
+  do {                                                                                                        \
+    if (part) hipLaunchKernelGGL((k_gemm_tn_short<KS_, true>), grid, dim3(GTHREADS), 0, s, g, per);           \
+    else hipLaunchKernelGGL((k_gemm_tn_short<KS_, false>), grid, dim3(GTHREADS), 0, s, g, per);               \
+  } while (0)
+    switch (ks) {
+      case 2: MAPL_SHORT(2); break;
+      case 3: MAPL_SHORT(3); break;
+      case 4: MAPL_SHORT(4); break;
+      case 5: MAPL_SHORT(5); break;
+      default: MAPL_SHORT(6); break;
     }
+#undef MAPL_SHORT
+    return hipGetLastError();
   }
+  // Few 128-token workgroups leave CUs idle: smaller tiles with a deeper ring.
+  // Measured (this kernel / deep, us): N = 256, K = 1088: 64 workgroups 19.6 /
+  // 10.5; K = 2112: 128: 36.0 / 27.0, 157: 33.9 / 37.5; N = 1024, K = 320: 128:
+  // 10.0 / 8.5, 188: 10.8 / 12.3.  With 128- or 64-column tiles: N = 128, K =
+  // 1024: 185: 18.7 / 15.8; N = 64, K = 480: 185: 9.0 / 8.1; N = 1152, K = 176:
+  // 216: 6.7 / 7.3.
+  const int bn = g.N % 256 == 0 ? 256 : g.N % 128 == 0 ? 128 : 64;
+  if ((int64_t)((g.M + GM - 1) / GM) * (g.N / bn) < (bn == 256 ? 140 : 192)) return launch_gemm_tn_deep(g, s);
   if (g.N % 256 == 0) return launch_ns<256>(g, s);
   if (g.N % 128 == 0) return launch_ns<128>(g, s);
   if (g.N % 64 == 0) return launch_ns<64>(g, s);

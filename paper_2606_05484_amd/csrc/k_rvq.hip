@@ -808,10 +808,10 @@ bool enc_rvq_fusable(int r, int L) { return r == FU_R && L >= 1 && L <= RQ_LMAX;
 
 hipError_t launch_enc_rvq(const TnArgs& g, const RvqArgs& a, hipStream_t s) {
   if (a.T <= 0) return hipSuccess;
-  if (!enc_rvq_fusable(a.r, a.L) || g.N != FU_R || g.M != a.T || g.kz != 0) return hipErrorInvalidValue;
-  if (g.Ka % 32 || g.Kg % 16 || g.Ka + g.Kg > g.ldw || g.lda % 8 || g.ldt % 8 || g.ldw % 8)
+  if (!enc_rvq_fusable(a.r, a.L) || g.N != FU_R || g.M != a.T) return hipErrorInvalidValue;
+  if (g.Ka % GK || g.Kg % 16 || g.Ka + g.Kg > g.ldw || g.lda % 8 || g.ldt % 8 || g.ldw % 8)
     return hipErrorInvalidValue;
-  const bool fullk = g.Ka % GK == 0 && g.Kg % GK == 0;
+  const bool fullk = g.Kg % GK == 0;
   dim3 grid((a.T + RQ_TOK - 1) / RQ_TOK);
   if (fullk)
     hipLaunchKernelGGL(k_enc_rvq<true>, grid, dim3(RQ_THREADS), 0, s, g, a);

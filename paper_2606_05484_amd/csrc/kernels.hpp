@@ -11,11 +11,8 @@ typedef uint16_t bf16_t;
 
 // ---------------------------------------------------------------- bf16 GEMM
 // out[t,n] = sum_{c<Ka} A[t,c] W[n,c] + sum_{i<Kg} T[ids[t],i] W[n,Ka+i]
-// Ka % 32 == 0, Kg % 16 == 0, ldw >= Ka + roundup(Kg,32) with zero padding,
-// lda, ldt, ldw multiples of 8 (16 B rows), N % 32 == 0.
-// Split-K: with kz > 0 (and Kg == 0) grid z-slice s covers columns
-// [s*kz, (s+1)*kz) of A and W and writes its own fp32 partial at out + s*out_z.
-// out_accum (fp32 output only) adds to the existing output instead of storing.
+// Ka % 64 == 0, Kg % 16 == 0, ldw >= Ka + Kg, lda, ldt, ldw multiples of 8
+// (16 B rows), N % 64 == 0.
 // With codes != null the first Ka columns of the token operand are not read
 // from A but gathered: sum_{l<L} C[l][codes[t][l]][c] (C fp32 [L][K][Ka],
 // codes [M][L] of code_bytes each, clamped to K-1, L <= 2), summed in fp32
@@ -27,11 +24,11 @@ struct TnArgs {
   const bf16_t* W; int64_t ldw;
   int M, N, Ka;
   void* out; int64_t ldo; int out_f32;
-  int kz; int64_t out_z; int out_accum;
   const void* codes; int code_bytes; const float* C; int L; int K;
 };
 hipError_t launch_gemm_tn(const TnArgs& g, hipStream_t s);
 bool gemm_tn_gathers(const TnArgs& g);
+hipError_t launch_gemm_tn_deep(const TnArgs& g, hipStream_t s);  // its kernel for few tiles
 
 // ---------------------------------------------------------------- fp32 GEMM
 // C[b](m,n) = alpha sum_k A[b](m,k) B[b](k,n) + beta Cin[b](m,n), all fp32; Cin may be null.

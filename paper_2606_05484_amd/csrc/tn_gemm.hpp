@@ -72,8 +72,8 @@ __device__ __forceinline__ void tn_products(f32x16_t (&acc)[2][BN / 64], uint32_
 
 // Epilogue of one 128 x BN output tile (columns nt BN ..): lane l holds
 // token (l % 32) of fragment i and, for q = 0..3, output columns
-// 8q + 4(l / 32) + 0..3 of fragment j.  fp32 results leave as 16 B stores
-// (optionally accumulating).  bf16: after the cross-half swap lane (t, h)
+// 8q + 4(l / 32) + 0..3 of fragment j.  fp32 results leave as 16 B stores.
+// bf16: after the cross-half swap lane (t, h)
 // holds the 16 B segment of token t covering columns 8(2q + h) .. +7 of
 // fragment j (q = 0, 1); segments are staged through STG_BYTES of LDS at
 // byte address stg (free for the duration: the caller syncs the workgroup
@@ -94,11 +94,7 @@ __device__ __forceinline__ void tn_epilogue(f32x16_t (&acc)[2][BN / 64], const T
           float* o = (float*)obase + (int64_t)t * g.ldo + nt * BN + wn * (BN / 2) + j * 32 + 4 * half;
 #pragma unroll
           for (int q = 0; q < 4; ++q) {
-            float4 v = make_float4(acc[i][j][4 * q], acc[i][j][4 * q + 1], acc[i][j][4 * q + 2], acc[i][j][4 * q + 3]);
-            if (g.out_accum) {
-              const float4 p = *(const float4*)(o + 8 * q);
-              v.x += p.x; v.y += p.y; v.z += p.z; v.w += p.w;
-            }
+            const float4 v = make_float4(acc[i][j][4 * q], acc[i][j][4 * q + 1], acc[i][j][4 * q + 2], acc[i][j][4 * q + 3]);
             *(float4*)(o + 8 * q) = v;
           }
         }
@@ -184,9 +180,7 @@ __device__ __forceinline__ void tn_mainloop(const TnArgs& g, int ntiles_per_wg, 
   const int m0 = blockIdx.x * GM;
   const int nt0 = blockIdx.y * ntiles_per_wg;
   const int ntiles = min(ntiles_per_wg, g.N / BN - nt0);
-  const int kz = g.kz > 0 ? g.kz : g.Ka;
-  const int kbase = g.kz > 0 ? blockIdx.z * g.kz : 0;
-  const int ka_steps = (kz + GK - 1) / GK;
+  const int ka_steps = g.Ka / GK;
   const int kg_steps = (g.Kg + GK - 1) / GK;
   const int KS = ka_steps + kg_steps;
   const int KSP = (KS + NS - 1) / NS * NS;      // padded: stage buffers repeat every tile
@@ -233,17 +227,17 @@ __device__ __forceinline__ void tn_mainloop(const TnArgs& g, int ntiles_per_wg, 
   // planned once (steps in order), then issued a few at a time between the
   // products of the step before (see compute): a burst of them would hold up
   // the wave's instruction stream while the memory pipeline drains it.
-  // FULLK: every K dimension is a multiple of GK, so each real step covers
-  // whole stages: a load takes the lane's fixed offset as its VGPR operand
-  // and the stage's column offset as its scalar operand (rows past the last
-  // token still fall outside the A resource and read zeros), and planning
-  // costs no vector arithmetic.  Otherwise per-lane checks select each
-  // offset or OOB.
+  // A load takes the lane's fixed offset as its VGPR operand and the stage's
+  // column offset as its scalar operand (rows past the last token still fall
+  // outside the A resource and read zeros), so planning costs no vector
+  // arithmetic.  Without FULLK the gathered width Kg ends inside its last
+  // stage: lanes whose 16-byte chunk lies past it load zeros, decided per
+  // stage for the two chunks a lane uses (by block parity).
   struct Plan {
     bf16_t *sa, *sw;
     int sA, sW;
     bool live, gathered;
-    uint32_t vA[FULLK ? 1 : ABLK], vW[FULLK ? 1 : WBLK];  // per-lane offsets (not FULLK)
+    bool ok0, ok1;  // not FULLK: this lane's chunk exists, per block parity
   };
   int pl_ks = 0, pl_nt = nt0;  // next step to plan
   auto plan_next = [&](bf16_t* sa, bf16_t* sw) {
@@ -262,30 +256,11 @@ __device__ __forceinline__ void tn_mainloop(const TnArgs& g, int ntiles_per_wg, 
     if (ks >= KS) ks -= KS;
     p.gathered = p.live && ks >= ka_steps;
     const int kc = p.gathered ? (ks - ka_steps) * GK : ks * GK;
-    const uint32_t aadd = (uint32_t)(p.gathered ? kc : kbase + kc) * 2u;
-    const int wcol0 = p.gathered ? g.Ka + kc : kbase + kc;
-    const uint32_t wadd = (uint32_t)nt * BN * (uint32_t)g.ldw * 2u + (uint32_t)wcol0 * 2u;
-    if constexpr (FULLK) {
-      p.sA = (int)aadd;
-      p.sW = (int)wadd;
-    } else {
-      const int alim = p.gathered ? g.Kg : kz;
-      const int wlim = p.gathered ? g.Ka + g.Kg : kbase + kz;
-      // this lane's first column in the stage, per block parity
-      const int col0 = kc + 8 * (int)lchp[0], col1 = kc + 8 * (int)lchp[1];
-      const int wc0 = wcol0 + 8 * (int)lchp[0], wc1 = wcol0 + 8 * (int)lchp[1];
-      const bool ok0 = col0 < alim, ok1 = col1 < alim;
-      const bool wok0 = wc0 < wlim && wc0 < g.ldw, wok1 = wc1 < wlim && wc1 < g.ldw;
-#pragma unroll
-      for (int j = 0; j < ABLK; ++j) {
-        const uint32_t o = p.gathered ? t_off[j] : a_off[j];
-        p.vA[j] = ((j & 1) ? ok1 : ok0) && o != OOB ? o + aadd : OOB;
-      }
-#pragma unroll
-      for (int j = 0; j < WBLK; ++j) p.vW[j] = ((j & 1) ? wok1 : wok0) ? w_off[j] + wadd : OOB;
-      p.sA = 0;
-      p.sW = 0;
-    }
+    p.sA = kc * 2;
+    p.sW = (int)((uint32_t)nt * BN * (uint32_t)g.ldw * 2u + (uint32_t)(p.gathered ? g.Ka + kc : kc) * 2u);
+    const int lim = p.gathered ? g.Kg - kc : GK;
+    p.ok0 = FULLK || 8 * (int)lchp[0] < lim;
+    p.ok1 = FULLK || 8 * (int)lchp[1] < lim;
     return p;
   };
   // loads [B0, B1) of a step: A (or anchor) block li < ABLK, else W block li - ABLK
@@ -298,12 +273,13 @@ __device__ __forceinline__ void tn_mainloop(const TnArgs& g, int ntiles_per_wg, 
         constexpr int LI = decltype(lic)::value;
         if constexpr (LI < ABLK) {
           const lds_ptr dst = (lds_ptr)(p.sa + (wave * ABLK + LI) * 512);
-          const uint32_t v = FULLK ? (GATH ? t_off[LI] : a_off[LI]) : p.vA[FULLK ? 0 : LI];
+          const uint32_t v = !GATH ? a_off[LI] : FULLK || ((LI & 1) ? p.ok1 : p.ok0) ? t_off[LI] : OOB;
           __builtin_amdgcn_raw_ptr_buffer_load_lds(GATH ? rt : ra, dst, 16, v, p.sA, 0, 0);
         } else {
           constexpr int J = LI - ABLK;
           const lds_ptr dst = (lds_ptr)(p.sw + (wave * WBLK + J) * 512);
-          __builtin_amdgcn_raw_ptr_buffer_load_lds(rw, dst, 16, FULLK ? w_off[J] : p.vW[FULLK ? 0 : J], p.sW, 0, 0);
+          const uint32_t v = !GATH || FULLK || ((J & 1) ? p.ok1 : p.ok0) ? w_off[J] : OOB;
+          __builtin_amdgcn_raw_ptr_buffer_load_lds(rw, dst, 16, v, p.sW, 0, 0);
         }
       });
     };
