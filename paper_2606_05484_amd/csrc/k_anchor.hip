@@ -2,9 +2,12 @@
 // Every token contributes a gradient row g[t] (from the GEMM kernels) to the
 // table row of its id; the rows are summed per id in a fixed order, so the
 // result is reproducible bit for bit (no floating-point atomics):
-//   1. a stable LSD radix sort of (id, token) pairs, 8-bit digits: per-tile
-//      digit histograms, one exclusive scan, a stable scatter whose ranks
-//      come from wave ballots;
+//   1. the (id, token) pairs ordered so that equal ids are adjacent and keep
+//      their token order.  Up to 32768 tokens: a bin per 256 ids, one
+//      workgroup per bin, beside the call's other preparation
+//      (k_anchor_prep); longer lists by a stable LSD radix sort, 8-bit digits
+//      (per-tile digit histograms, one exclusive scan, a stable scatter).
+//      Ranks come from wave ballots in both;
 //   2. a segmented sum over the sorted order in 64-position sub-chunks, one
 //      wave each, walking its positions in order; a segment that crosses a
 //      sub-chunk boundary leaves its pieces in per-sub-chunk slots;
@@ -23,13 +26,169 @@ namespace {
 constexpr int RS_THREADS = 256, RS_TILE = 512, RS_ROUNDS = RS_TILE / RS_THREADS;
 constexpr int SEG = 64;  // sorted positions per sub-chunk
 
-// W[i][c] = B[i][c] for i < k, c < K, zero for the padding rows k <= i < kp.
-__global__ void k_pad_rows_bf16(const bf16_t* __restrict__ B, int k, int K, int kp, bf16_t* __restrict__ W) {
-  const int64_t n = (int64_t)kp * K;
-  for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < n; e += (int64_t)gridDim.x * blockDim.x) {
-    const int i = (int)(e / K);
-    W[e] = i < k ? B[e] : (bf16_t)0;
+// The preparation of one call as one launch of 1024-thread workgroups, by
+// block: the sort (one per bin of ids), then the padded or projected
+// companion W, then the zeroing of dA.  Each was a launch of its own of 3 to
+// 6 us, and the radix sort six (T = 8192: 25 us).
+constexpr int AP_THREADS = 1024, AP_WAVES = AP_THREADS / 64;
+
+// Bin b of the sort: ids with id % nbins == b (nbins a power of two, at
+// least V / 256, so id / nbins has 8 bits), or b == nbins for ids outside
+// [0, V), which go last as 0x7fffffff.  The workgroup reads every id (they
+// sit in the L2: 32 KB at T = 8192), so it knows its offset in the result
+// and lists its own tokens in order without any exchange between workgroups;
+// the list (all n tokens in the worst case) is then placed by its 8-bit
+// digit: the waves' counts, their scan (digit-major), and each wave's
+// positions 64 at a time, lanes of equal digit ranked by ballots.
+template <int RPT>
+__device__ __forceinline__ void sort_bin(const AnchorPrepArgs& a, int b, uint32_t* list, uint32_t (*cnt)[256], int* tot) {
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int base = wave * 64 * RPT + lane;
+  const int sh = __builtin_ctz(a.nbins);
+  int x[RPT];
+#pragma unroll
+  for (int j = 0; j < RPT; ++j) x[j] = base + 64 * j < a.n ? a.ids[base + 64 * j] : -1;
+  auto bin = [&](int id) { return (unsigned)id < (unsigned)a.V ? id & (a.nbins - 1) : a.nbins; };
+  int own = 0, lower = 0;
+#pragma unroll
+  for (int j = 0; j < RPT; ++j) {
+    const bool ok = base + 64 * j < a.n;
+    const int q = bin(x[j]);
+    own += __popcll(__ballot(ok && q == b));
+    lower += __popcll(__ballot(ok && q < b));
   }
+  if (lane == 0) {
+    tot[wave] = own;
+    tot[AP_WAVES + wave] = lower;
+  }
+  for (int i = tid; i < AP_WAVES * 256; i += AP_THREADS) (&cnt[0][0])[i] = 0;
+  __syncthreads();
+  int at = 0, m = 0, off = 0;
+#pragma unroll
+  for (int w = 0; w < AP_WAVES; ++w) {
+    at += w < wave ? tot[w] : 0;
+    m += tot[w];
+    off += tot[AP_WAVES + w];
+  }
+  if (m == 0) return;  // workgroup-uniform
+  const uint64_t below = (1ull << lane) - 1ull;
+#pragma unroll
+  for (int j = 0; j < RPT; ++j) {
+    const bool mine = base + 64 * j < a.n && bin(x[j]) == b;
+    const uint64_t sel = __ballot(mine);
+    const uint32_t dg = b < a.nbins ? (uint32_t)x[j] >> sh : 0u;
+    if (mine) list[at + __popcll(sel & below)] = dg << 24 | (uint32_t)(base + 64 * j);
+    at += __popcll(sel);
+  }
+  __syncthreads();
+  const int per = (m + AP_THREADS - 1) / AP_THREADS * 64, i0 = wave * per, i1 = min(m, i0 + per);
+  for (int i = i0 + lane; i < i1; i += 64) atomicAdd(&cnt[wave][list[i] >> 24], 1u);
+  __syncthreads();
+  // exclusive offsets, digit-major: thread d < 256 its digit's total, a scan
+  // over the digits by wave shuffles, then the waves in order
+  uint32_t sum = 0;
+  if (tid < 256) {
+#pragma unroll
+    for (int w = 0; w < AP_WAVES; ++w) sum += cnt[w][tid];
+  }
+  uint32_t inc = sum;
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) {
+    const uint32_t v = __shfl_up(inc, o, WAVE);
+    if (lane >= o) inc += v;
+  }
+  if (tid < 256 && lane == 63) tot[wave] = (int)inc;
+  __syncthreads();
+  if (tid < 256) {
+    uint32_t run = inc - sum;
+    for (int w = 0; w < wave; ++w) run += (uint32_t)tot[w];
+#pragma unroll
+    for (int w = 0; w < AP_WAVES; ++w) {
+      const uint32_t c = cnt[w][tid];
+      cnt[w][tid] = run;
+      run += c;
+    }
+  }
+  __syncthreads();
+  uint32_t* mine = cnt[wave];
+  for (int i = i0; i < i1; i += 64) {  // wave-uniform
+    const bool ok = i + lane < i1;
+    const uint32_t e = ok ? list[i + lane] : 0u, dg = e >> 24;
+    uint64_t peers = __ballot(ok);
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+      const bool bit = (dg >> k) & 1u;
+      const uint64_t set = __ballot(bit);
+      peers &= bit ? set : ~set;
+    }
+    const uint32_t pos = mine[dg];
+    __builtin_amdgcn_wave_barrier();  // every lane has read its digit's position
+    if (ok && (peers & below) == 0) mine[dg] = pos + (uint32_t)__popcll(peers);
+    __builtin_amdgcn_wave_barrier();
+    if (ok) {
+      const int p = off + (int)pos + __popcll(peers & below);
+      a.skey[p] = b < a.nbins ? (int32_t)(dg << sh | (uint32_t)b) : 0x7fffffff;
+      a.sval[p] = (int32_t)(e & 0xFFFFFFu);
+    }
+  }
+}
+
+// W tile rows i0 .. i0+15, columns c0 .. c0+15 of bf16(B U~) (U~ = bf16(U)
+// where it enters the matrix units), rows from k on zero: the sixteen waves
+// take every sixteenth 32-wide k-step and their partial tiles are summed in
+// wave order.
+__device__ __forceinline__ void proj_tile(const AnchorPrepArgs& a, int i0, int c0, float* part) {
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, quad = lane >> 4;
+  const int row = min(i0 + (lane & 15), a.k - 1), c = c0 + (lane & 15);
+  f32x4_t acc = f32x4_t{};
+  for (int kb = 32 * wave; kb < a.d; kb += 32 * AP_WAVES) {
+    const uint4 p = *(const uint4*)(a.B + (int64_t)row * a.d + kb + 8 * quad);
+    float q[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) q[e] = a.U[(int64_t)(kb + 8 * quad + e) * a.K + c];
+    acc = mfma16x16x32(p, make_uint4(pack_bf2(q[0], q[1]), pack_bf2(q[2], q[3]), pack_bf2(q[4], q[5]), pack_bf2(q[6], q[7])),
+                       acc);
+  }
+#pragma unroll
+  for (int e = 0; e < 4; ++e) part[wave * 256 + (4 * quad + e) * 16 + (lane & 15)] = acc[e];
+  __syncthreads();
+  if (tid < 256) {
+    float v = part[tid];
+#pragma unroll
+    for (int w = 1; w < AP_WAVES; ++w) v += part[w * 256 + tid];
+    const int i = i0 + (tid >> 4);
+    if (i < a.kp) a.W[(int64_t)i * a.K + c0 + (tid & 15)] = i < a.k ? (bf16_t)f2bf(v) : (bf16_t)0;
+  }
+}
+
+template <int RPT>
+__global__ __launch_bounds__(AP_THREADS) void k_anchor_prep(AnchorPrepArgs a) {
+  __shared__ uint32_t xch[RPT > 4 ? RPT * AP_THREADS : 4 * AP_THREADS];  // also proj_tile's partial tiles
+  __shared__ uint32_t cnt[AP_WAVES][256];
+  __shared__ int tot[2 * AP_WAVES];
+  int b = blockIdx.x;
+  if constexpr (RPT > 0) {
+    if (b <= a.nbins) {
+      sort_bin<RPT>(a, b, xch, cnt, tot);
+      return;
+    }
+    b -= a.nbins + 1;
+  }
+  if (b < a.wblocks) {
+    if (a.U) {
+      const int nc = a.K / 16;
+      proj_tile(a, b / nc * 16, b % nc * 16, (float*)xch);
+    } else {  // W[i][c] = B[i][c], rows from k on zero; 8 columns per thread
+      const int64_t e = ((int64_t)b * AP_THREADS + threadIdx.x) * 8;
+      if (e < (int64_t)a.kp * a.K)
+        *(uint4*)(a.W + e) = e < (int64_t)a.k * a.K ? *(const uint4*)(a.B + e) : make_uint4(0u, 0u, 0u, 0u);
+    }
+    return;
+  }
+  b -= a.wblocks;
+  const int64_t i = (int64_t)b * AP_THREADS + threadIdx.x;
+  if (i < a.zero16) ((uint4*)a.dA)[i] = make_uint4(0u, 0u, 0u, 0u);
 }
 
 __global__ __launch_bounds__(RS_THREADS) void k_radix_hist(const int32_t* __restrict__ keys, int n, int shift,
@@ -160,69 +319,92 @@ __device__ __forceinline__ void seg_store(float* __restrict__ row, const float (
 template <int NC>
 __global__ __launch_bounds__(256) void k_seg_partial(AnchorSegArgs a) {
   constexpr int BR = 64 / NC;
+  __shared__ float stage[4][64 * 64];  // each wave its own part: no barrier
   const int lane = threadIdx.x & 63;
-  const int s = blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (s >= a.nsub) return;  // wave-uniform
-  const int p0 = s * SEG, p1 = min(a.n, p0 + SEG);
-  // -1 marks "no neighbour"; ids are non-negative (negative ones are never written)
-  const int prev_id = p0 > 0 ? a.skey[p0 - 1] : -1;
-  const int next_id = p1 < a.n ? a.skey[p1] : -1;
+  // wave-uniform, and known to be: the walk below branches on scalars
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), s = blockIdx.x * 4 + wave;
+  if (s >= a.nsub) return;
+  const int p0 = s * SEG, np = min(a.n - p0, SEG);
+  // lane u: position p0 + u, its id and token; a position ends a segment
+  // where the next id differs (-1 and -2 mark "none"; ids are non-negative)
+  const int idl = lane < np ? a.skey[p0 + lane] : -2;
+  const int tl = lane < np ? a.sval[p0 + lane] : 0;
+  const int prev_id = p0 > 0 ? __builtin_amdgcn_readfirstlane(a.skey[p0 - 1]) : -1;
+  const int next_id = p0 + np < a.n ? __builtin_amdgcn_readfirstlane(a.skey[p0 + np]) : -1;
+  int nid = __shfl_down(idl, 1, WAVE);
+  if (lane == np - 1) nid = next_id;
+  const uint64_t ends = __ballot(lane < np && (nid != idl || lane == np - 1));
+  // the first segment continues the previous sub-chunk's (its sum goes to the
+  // head slot), the last goes on in the next one's (tail slot)
+  const int id0 = __builtin_amdgcn_readlane(idl, 0), idn = __builtin_amdgcn_readlane(idl, np - 1);
+  const bool before = prev_id == id0, after = next_id == idn;
+  const bool through = before && after && __builtin_ctzll(ends) == np - 1;  // one segment, from before to after
   if (lane == 0) {
-    a.head_id[s] = -1;
-    a.head_thru[s] = 0;
-    a.tail_id[s] = -1;
+    a.head_id[s] = before ? id0 : -1;
+    a.head_thru[s] = through ? 1 : 0;
+    a.tail_id[s] = after && !through ? idn : -1;
   }
+  float* rows = stage[wave];
   float acc[NC];
 #pragma unroll
   for (int q = 0; q < NC; ++q) acc[q] = 0.f;
-  int pstart = p0;
-  for (int pb = p0; pb < p1; pb += BR) {
-    // the batch's ids, tokens and rows are requested before any is summed
-    int id[BR], t[BR];
-    float v[BR][NC];
-#pragma unroll
-    for (int u = 0; u < BR; ++u) {
-      const int p = min(pb + u, p1 - 1);
-      id[u] = a.skey[p];
-      t[u] = a.sval[p];
-    }
-#pragma unroll
-    for (int u = 0; u < BR; ++u) {
-      const float* gr = a.g + (int64_t)t[u] * a.ldg;
-#pragma unroll
-      for (int q = 0; q < NC; ++q) {
-        const int c = lane + 64 * q;
-        v[u][q] = c < a.k ? gr[c] : 0.f;
+  // Each segment's sum has one store, its place chosen by scalar selects: a
+  // lone wave pays some 30 cycles per branch taken, and a walk with a branch
+  // per row and place took 190 to 430 cycles per row (T = 8192, k = 64: 14 us
+  // of the launch's 18; 11.5 in all now).
+  auto walk = [&](auto addc) {
+    constexpr bool ADD = decltype(addc)::value;
+    bool first = before;  // the next sum is the head piece
+    for (int pb = 0; pb < np; pb += BR) {
+      // the batch's rows go to LDS straight from memory, all on their way
+      // before the first is used: 16 bytes per lane and load
+      static_assert(BR * NC == 64, "a batch is 4096 floats");
+#pragma unroll 1
+      for (int i = 0; i < 16; ++i) {
+        const int f = i * 256 + lane * 4, u = f / (64 * NC), c = f % (64 * NC);
+        const int t = __shfl(tl, min(pb + u, np - 1), WAVE);
+        const float* src = a.g + (int64_t)t * a.ldg + min(c, (int)a.ldg - 4);  // columns past k are not stored
+        __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)src,
+                                         (__attribute__((address_space(3))) void*)(rows + i * 256), 16, 0, 0);
       }
-    }
+      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+      const int pe = min(pb + BR, np);
+      float cur[NC];
 #pragma unroll
-    for (int u = 0; u < BR; ++u) {
-      const int p = pb + u;
-      if (p >= p1) break;
+      for (int q = 0; q < NC; ++q) cur[q] = rows[q * 64 + lane];
+      for (int p = pb; p < pe;) {
+        const int end = p + __builtin_ctzll(ends >> p);  // the segment's last position
+        const int stop = min(end, pe - 1);
+        for (; p <= stop; ++p) {
+          const float* nx = rows + min(p - pb + 1, BR - 1) * NC * 64;
 #pragma unroll
-      for (int q = 0; q < NC; ++q) acc[q] += v[u][q];
-      const int nid = p + 1 < p1 ? (u + 1 < BR ? id[u + 1] : a.skey[p + 1]) : next_id;
-      if (nid == id[u] && p + 1 < p1) continue;  // the segment goes on inside the sub-chunk
-      const bool before = pstart == p0 && prev_id == id[u];
-      const bool after = p + 1 == p1 && next_id == id[u];
-      if (!before && !after) {
-        if ((unsigned)id[u] < (unsigned)a.V)  // an id outside [0, V) is a caller error: skipped
-          seg_store<NC>(a.dA + (int64_t)id[u] * a.k, acc, a.k, lane, a.scale, a.accumulate);
-      } else if (before) {
-        seg_store<NC>(a.headp + (int64_t)s * a.k, acc, a.k, lane, 1.f, 0);
-        if (lane == 0) {
-          a.head_id[s] = id[u];
-          a.head_thru[s] = after ? 1 : 0;
+          for (int q = 0; q < NC; ++q) {
+            acc[q] += cur[q];
+            cur[q] = nx[q * 64 + lane];
+          }
         }
-      } else {
-        seg_store<NC>(a.tailp + (int64_t)s * a.k, acc, a.k, lane, 1.f, 0);
-        if (lane == 0) a.tail_id[s] = id[u];
-      }
+        if (end > stop) break;  // it goes on in the next batch
+        const int id = __builtin_amdgcn_readlane(idl, end);
+        const bool last = after && end == np - 1, piece = first || last;
+        const bool ok = piece || (unsigned)id < (unsigned)a.V;  // an id outside [0, V) is a caller error: skipped
+        float* row = piece ? (first ? a.headp : a.tailp) + (int64_t)s * a.k : a.dA + (int64_t)id * a.k;
+        const float scale = piece ? 1.f : a.scale;
 #pragma unroll
-      for (int q = 0; q < NC; ++q) acc[q] = 0.f;
-      pstart = p + 1;
+        for (int q = 0; q < NC; ++q) {
+          const int c = lane + 64 * q;
+          if (c < (ok ? a.k : 0)) {
+            float x = scale * acc[q];
+            if (ADD) x += piece ? 0.f : row[c];
+            row[c] = x;
+          }
+          acc[q] = 0.f;
+        }
+        first = false;
+      }
     }
-  }
+  };
+  if (a.accumulate) walk(std::true_type{});
+  else walk(std::false_type{});
 }
 
 // Segments that cross sub-chunk boundaries, one workgroup per sub-chunk s
@@ -297,11 +479,26 @@ void launch_segsum_nc(const AnchorSegArgs& a, hipStream_t s) {
 
 }  // namespace
 
-hipError_t launch_pad_rows_bf16(const bf16_t* B, int k, int K, int kp, bf16_t* W, hipStream_t s) {
-  const int64_t n = (int64_t)kp * K;
-  if (n <= 0) return hipSuccess;
-  const int blocks = (int)((n + 255) / 256 < 4096 ? (n + 255) / 256 : 4096);
-  hipLaunchKernelGGL(k_pad_rows_bf16, dim3(blocks), dim3(256), 0, s, B, k, K, kp, W);
+// A list of 32768 tokens fits the LDS beside the counts; 512 bins (V up to
+// 131072) read the ids 512 times, 64 MB from the L2s at most.
+bool anchor_sort_fits(int64_t n, int64_t V) { return n <= 32 * AP_THREADS && V <= 131072; }
+
+hipError_t launch_anchor_prep(const AnchorPrepArgs& a, hipStream_t s) {
+  AnchorPrepArgs g = a;
+  const bool sort = a.skey != nullptr;
+  if (sort && !anchor_sort_fits(a.n, a.V)) return hipErrorInvalidValue;
+  if (a.W && (a.K % 16 || a.kp % 16 || a.d % 32)) return hipErrorInvalidValue;
+  g.wblocks = !a.W ? 0 : a.U ? (a.kp / 16) * (a.K / 16) : (int)(((int64_t)a.kp * a.K / 8 + AP_THREADS - 1) / AP_THREADS);
+  g.nbins = 1;
+  while (g.nbins * 256 < g.V) g.nbins *= 2;
+  const int64_t blocks = (sort ? g.nbins + 1 : 0) + g.wblocks + (a.zero16 + AP_THREADS - 1) / AP_THREADS;
+  if (blocks <= 0) return hipSuccess;
+  const dim3 grid((unsigned)blocks), thr(AP_THREADS);
+  if (!sort) hipLaunchKernelGGL(k_anchor_prep<0>, grid, thr, 0, s, g);
+  else if (a.n <= 2 * AP_THREADS) hipLaunchKernelGGL(k_anchor_prep<2>, grid, thr, 0, s, g);
+  else if (a.n <= 8 * AP_THREADS) hipLaunchKernelGGL(k_anchor_prep<8>, grid, thr, 0, s, g);
+  else if (a.n <= 16 * AP_THREADS) hipLaunchKernelGGL(k_anchor_prep<16>, grid, thr, 0, s, g);
+  else hipLaunchKernelGGL(k_anchor_prep<32>, grid, thr, 0, s, g);
   return hipGetLastError();
 }
 

@@ -191,10 +191,9 @@ struct PrepJob {
   AssembleArgs asm_args;
   // PJ_GATHER
   const bf16_t* A; int k; const int32_t* ids; int V, T; bf16_t* out;
-  // PJ_SMALL_GEMM: dst[c*ldd + off + i] (dst_rows = 0) or dst[i*ldd + off + c]
-  // (dst_rows = 1) = bf16(scale * sum_j P[i][j] bf16(Q(j, c))),
+  // PJ_SMALL_GEMM: dst[c*ldd + off + i] = bf16(scale * sum_j P[i][j] bf16(Q(j, c))),
   // Q(j, c) = Q[j*ldq + c] (qt = 0) or Q[c*ldq + j] (qt = 1)
-  const void* P; int64_t ldp; const float* Q; int64_t ldq; int qt, M, N, Kd, dst_rows;
+  const void* P; int64_t ldp; const float* Q; int64_t ldq; int qt, M, N, Kd;
 };
 constexpr int PREP_MAX_JOBS = 4;
 struct PrepBatch {
@@ -303,8 +302,21 @@ hipError_t launch_codebook_unpack(const float* buf, const int32_t* rows, int L, 
                                   hipStream_t s);
 
 // ---------------------------------------------------------------- anchor-table gradient
-// W[i][c] = B[i][c] (i < k), 0 for k <= i < kp; c < K; both row-major with K columns.
-hipError_t launch_pad_rows_bf16(const bf16_t* B, int k, int K, int kp, bf16_t* W, hipStream_t s);
+// One launch for what a call needs before its products and sums:
+//   skey/sval (optional): the (ids[i], i) with equal ids adjacent and in
+//     order of i, where anchor_sort_fits(n, V); ids outside [0, V) last, as
+//     0x7fffffff
+//   W (optional): [kp, K] bf16, rows from k on zero: B [k, K], or with U
+//     (fp32 [d, K]) bf16(B U~), B [k, d], U~ = bf16(U)
+//   dA: the first zero16 16-byte pieces set to zero
+struct AnchorPrepArgs {
+  const int32_t* ids; int n, V; int32_t* skey; int32_t* sval;
+  const bf16_t* B; const float* U; bf16_t* W; int k, kp, K, d;
+  float* dA; int64_t zero16;
+  int wblocks, nbins;  // set by the launcher
+};
+bool anchor_sort_fits(int64_t n, int64_t V);
+hipError_t launch_anchor_prep(const AnchorPrepArgs& a, hipStream_t s);
 // Stable radix sort of (ids[i], i) by id over `passes` 8-bit digits; buffers of
 // n int32 each (k0/v0, k1/v1 ping-pong) and hist of 256 * radix_tiles(n) ints;
 // *skey / *sval receive the sorted ids and token indices.

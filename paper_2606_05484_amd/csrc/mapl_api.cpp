@@ -1241,27 +1241,40 @@ extern "C" int mapl_anchor_bwd(const mapl_codec_desc* desc, int side, const void
   if (st) return st;
   if ((st = check_ws(ws, ws_bytes, Lo.total))) return st;
   hipStream_t s = (hipStream_t)stream;
-  if (!accumulate) LAUNCH("anchor_bwd:zero", launch_zero_bytes(dA, (int64_t)na, s));
-  if (T == 0) return MAPL_OK;
-  if (debug_ids()) {
+  if (T > 0 && debug_ids()) {
     Layout tmp;
     tmp.flag = Lo.hid;  // the head-id slots are written later in the call
     if ((st = run_id_check(ids, T, D.V, ws, tmp, s))) return st;
   }
+  // 1. one launch: dA cleared, the product's second operand, and the tokens
+  //    sorted by id (stable) where one workgroup holds them
+  const bool bf = D.x_dtype == MAPL_BF16;
+  AnchorPrepArgs pa{};
+  pa.dA = dA;
+  pa.zero16 = accumulate ? 0 : (int64_t)(na / 16);
+  const bf16_t* W = (const bf16_t*)B;  // whole 64-row blocks serve as they are
+  const int32_t *skey = nullptr, *sval = nullptr;
+  if (T > 0) {
+    if (bf && (need_u || Lo.kp > k)) {
+      pa.W = at<bf16_t>(ws, Lo.w);
+      pa.B = (const bf16_t*)B;
+      pa.U = need_u ? U : nullptr;
+      pa.k = (int)k; pa.kp = Lo.kp; pa.K = Lo.K; pa.d = (int)d;
+      W = pa.W;
+    }
+    if (anchor_sort_fits(T, D.V)) {
+      pa.ids = ids; pa.n = (int)T; pa.V = (int)D.V;
+      pa.skey = at<int32_t>(ws, Lo.k0); pa.sval = at<int32_t>(ws, Lo.v0);
+      skey = pa.skey; sval = pa.sval;
+    }
+  }
+  LAUNCH("anchor_bwd:prep", launch_anchor_prep(pa, s));
+  if (T == 0) return MAPL_OK;
   float* g = at<float>(ws, Lo.g);
-  // 1. per-token gradient rows g[t] (the sign of the sender's term is applied
+  // 2. per-token gradient rows g[t] (the sign of the sender's term is applied
   //    in the reduction): sender  dZ (B_s U)^T (ambient) or dZ B_s^T (coord),
   //    receiver dXhat B_r^T (ambient) or dZhat B_r^T (coord)
-  if (D.x_dtype == MAPL_BF16) {
-    bf16_t* W = at<bf16_t>(ws, Lo.w);
-    if (need_u) {
-      if (Lo.kp > k) LAUNCH("anchor_bwd:zero_w", launch_zero_bytes(W + k * r, (int64_t)(Lo.kp - k) * r * 2, s));
-      PrepJob j = prep_job_small_gemm((const bf16_t*)B, d, U, r, 0, (int)k, (int)r, (int)d, 1.f, W, r, 0);
-      j.dst_rows = 1;
-      LAUNCH("anchor_bwd:prep", launch_prep_batch(&j, 1, s));
-    } else {
-      LAUNCH("anchor_bwd:prep", launch_pad_rows_bf16((const bf16_t*)B, (int)k, Lo.K, Lo.kp, W, s));
-    }
+  if (bf) {
     TnArgs gg{};
     gg.A = (const bf16_t*)dY; gg.lda = Lo.K; gg.Ka = Lo.K;
     gg.W = W; gg.ldw = Lo.K;
@@ -1285,11 +1298,11 @@ extern "C" int mapl_anchor_bwd(const mapl_codec_desc* desc, int side, const void
     e.C = g; e.sCm = Lo.kp; e.sCn = 1;
     LAUNCH("anchor_bwd:gemm_f32", launch_gemm_f32(e, s));
   }
-  // 2. tokens sorted by id (stable), 3. per-id sums in sorted order
-  const int32_t *skey = nullptr, *sval = nullptr;
-  LAUNCH("anchor_bwd:sort", launch_sort_ids(ids, (int)T, Lo.passes, at<int>(ws, Lo.hist), at<int32_t>(ws, Lo.k0),
-                                            at<int32_t>(ws, Lo.v0), at<int32_t>(ws, Lo.k1), at<int32_t>(ws, Lo.v1),
-                                            &skey, &sval, s));
+  // 3. longer token lists sorted here, 4. per-id sums in sorted order
+  if (!skey)
+    LAUNCH("anchor_bwd:sort", launch_sort_ids(ids, (int)T, Lo.passes, at<int>(ws, Lo.hist), at<int32_t>(ws, Lo.k0),
+                                              at<int32_t>(ws, Lo.v0), at<int32_t>(ws, Lo.k1), at<int32_t>(ws, Lo.v1),
+                                              &skey, &sval, s));
   AnchorSegArgs a{};
   a.g = g; a.ldg = Lo.kp; a.k = (int)k;
   a.skey = skey; a.sval = sval; a.n = (int)T;
