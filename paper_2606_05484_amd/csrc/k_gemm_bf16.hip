@@ -437,11 +437,12 @@ hipError_t launch_gemm_tn(const TnArgs& g, hipStream_t s) {
   // Few 128-token workgroups leave CUs idle: smaller tiles with a deeper ring.
   // Measured (this kernel / deep, us): N = 256, K = 1088: 64 workgroups 19.6 /
   // 10.5; K = 2112: 128: 36.0 / 27.0, 157: 33.9 / 37.5; N = 1024, K = 320: 128:
-  // 10.0 / 8.5, 188: 10.8 / 12.3.  With 128- or 64-column tiles: N = 128, K =
-  // 1024: 185: 18.7 / 15.8; N = 64, K = 480: 185: 9.0 / 8.1; N = 1152, K = 176:
-  // 216: 6.7 / 7.3.
+  // 10.0 / 8.5, 188: 10.8 / 12.3.  128-column tiles: K = 1040: 64: 15.6 / 8.5; K =
+  // 1088: 125: 15.4 / 12.2; K = 1024: 185: 18.7 / 15.8; K = 256: 128: 10.5 / 11.8.
+  // 64-column tiles: 8: 10.1 / 7.6; 128: 8.0 / 8.7; 142 (K = 1856): 17.7 / 17.8.
   const int bn = g.N % 256 == 0 ? 256 : g.N % 128 == 0 ? 128 : 64;
-  if ((int64_t)((g.M + GM - 1) / GM) * (g.N / bn) < (bn == 256 ? 140 : 192)) return launch_gemm_tn_deep(g, s);
+  const int below = bn == 256 ? 140 : bn == 128 && g.Ka + g.Kg >= 512 ? 192 : 100;
+  if ((int64_t)((g.M + GM - 1) / GM) * (g.N / bn) < below) return launch_gemm_tn_deep(g, s);
   if (g.N % 256 == 0) return launch_ns<256>(g, s);
   if (g.N % 128 == 0) return launch_ns<128>(g, s);
   if (g.N % 64 == 0) return launch_ns<64>(g, s);

@@ -60,16 +60,15 @@ __device__ __forceinline__ void transpose_tile(int bx, int by, const void* __res
 
 // The power of two that takes a round's codebook into the screen's units:
 // the largest of a sample of its coordinates (four columns, other ones for
-// each codeword, of up to 1024 codewords) lands in [2^5, 2^6).  fp16 then
+// each codeword, of up to 256 codewords) lands in [2^5, 2^6).  fp16 then
 // keeps 11 bits of every coordinate from 2^-19 of that up to 2^10 times it.
-// Every block computes the same value from the same sample (16 KB, read
+// Every block computes the same value from the same sample (4 KB, read
 // while the block's rows are on their way); a poor sample costs speed only,
 // because the margins use the rounding errors that really occurred.
 __device__ __forceinline__ float rvq_round_scale(const float* __restrict__ C, int K, int r, float* red) {
-  const int n = min(K, 1024), q4 = r / 4;
+  const int n = min(K, 256), q4 = r / 4;
   const int64_t stride = K / n;
   float m = 0.f;
-#pragma unroll 4
   for (int i = threadIdx.x; i < n; i += 256) {
     const float4 v = *(const float4*)(C + (int64_t)i * stride * r + 4 * ((i * 17) % q4));
     m = fmaxf(m, fmaxf(fmaxf(fabsf(v.x), fabsf(v.y)), fmaxf(fabsf(v.z), fabsf(v.w))));
@@ -102,18 +101,27 @@ __device__ __forceinline__ void prep_codebook_block(int bx, const float* __restr
   const int l = min(w / (nch * 64), L - 1), slot = w % (nch * 64);
   const int j = slot;  // codeword index within stage l
   const int cols = rvq_cb_cols(r);
+  // the row's values are requested before the sample, so that they are there
+  // when the scale is (r <= 256: the screen's ranks)
+  constexpr int QMAX = 4;
+  float x[QMAX];
+#pragma unroll
+  for (int q = 0; q < QMAX; ++q) {
+    const int c = lane + 64 * q;
+    x[q] = j < K && w < L * nch * 64 && c < r ? C[((int64_t)l * K + j) * r + c] : 0.f;
+  }
   const float scale = rvq_round_scale(C + (int64_t)l * K * r, K, r, red);
+  if (w >= L * nch * 64) return;
   float s = 0.f, es = 0.f;
-  if (j < K) {
-    const float* row = C + ((int64_t)l * K + j) * r;
-    for (int c = lane; c < r; c += 64) {
-      const float v = row[c] * scale;
-      s += v * v;
-      const uint32_t vb = pack_h2(fminf(fmaxf(v, -65504.f), 65504.f), 0.f) & 0xFFFFu;
-      const float d = v - h2f(vb);  // the rounding (or saturation) error
-      es += d * d;
-      Cb[((int64_t)l * K + j) * cols + c] = (bf16_t)vb;
-    }
+#pragma unroll
+  for (int q = 0; q < QMAX; ++q) {
+    const int c = lane + 64 * q;
+    const float v = x[q] * scale;
+    s += v * v;
+    const uint32_t vb = pack_h2(fminf(fmaxf(v, -65504.f), 65504.f), 0.f) & 0xFFFFu;
+    const float d = v - h2f(vb);  // the rounding (or saturation) error
+    es += d * d;
+    if (j < K && c < r) Cb[((int64_t)l * K + j) * cols + c] = (bf16_t)vb;
   }
   s = wave_sum(s);
   es = wave_sum(es);
@@ -324,10 +332,6 @@ __global__ void k_transpose_into(const void* __restrict__ src, int src_f32, int 
                                  float scale, bf16_t* __restrict__ dst, int64_t ldd, int off) {
   transpose_tile(blockIdx.x, blockIdx.y, src, src_f32, rows, cols, lds, scale, dst, ldd, off);
 }
-__global__ void k_prep_codebook(const float* __restrict__ C, int L, int K, int r, bf16_t* __restrict__ Cb,
-                                float* __restrict__ meta, float* __restrict__ scale) {
-  prep_codebook_block(blockIdx.x, C, L, K, r, Cb, meta, scale);
-}
 __global__ void k_assemble(AssembleArgs a) { assemble_block(blockIdx.x, a); }
 __global__ void k_gather_rows_bf16(const bf16_t* __restrict__ A, int k, const int32_t* __restrict__ ids, int V,
                                    int T, bf16_t* __restrict__ out) {
@@ -448,15 +452,6 @@ hipError_t launch_transpose_into(const void* src, int src_f32, int rows, int col
   return hipGetLastError();
 }
 
-hipError_t launch_prep_codebook(const float* C, int L, int K, int r, bf16_t* Cb, float* meta, float* scale,
-                                hipStream_t s) {
-  const int64_t slots = (int64_t)L * ((K + 63) / 64) * 64;
-  if (slots <= 0) return hipSuccess;
-  hipLaunchKernelGGL(k_prep_codebook, dim3((unsigned)((slots + 3) / 4)), dim3(256), 0, s, C, L, K, r, Cb, meta,
-                     scale);
-  return hipGetLastError();
-}
-
 hipError_t launch_assemble(const AssembleArgs& a, hipStream_t s) {
   if (a.T <= 0) return hipSuccess;
   if (a.r % 8 || a.ldo % 8 || (a.A != nullptr && a.k % 8)) return hipErrorInvalidValue;
@@ -496,7 +491,7 @@ PrepJob prep_job_transpose(const void* src, int src_f32, int rows, int cols, int
 }
 
 PrepJob prep_job_codebook(const float* C, int L, int K, int r, bf16_t* Cb, float* meta, float* scale) {
-  PrepJob j{};
+  PrepJob j{};  // r <= 256 (prep_codebook_block)
   j.kind = PJ_CODEBOOK;
   j.C = C; j.L = L; j.K = K; j.r = r; j.Cb = Cb; j.meta = meta; j.cscale = scale;
   j.blocks = (int)(((int64_t)L * ((K + 63) / 64) * 64 + 3) / 4);

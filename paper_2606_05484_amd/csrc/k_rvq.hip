@@ -19,13 +19,14 @@
 //           scores a lane sees per tile, so a plain float min / med3 also
 //           yields the position; the tiles of the two smallest are tracked
 //           per tile.
-//   pass 1  per lane: the three smallest keys.  The nearest codeword j*
+//   pass 1  per lane: the two smallest keys and a lower bound of the third.
+//           The nearest codeword j*
 //           satisfies L_j* <= s_j* <= s_j1 <= U = L_j1 + (1 + 1.03) Delta_j1
 //           for the smallest key j1, so it is among {j : L_j <= U}: a
 //           single codeword when the token's second key exceeds U (final),
 //           the first and second keys of the two lane halves where both
-//           third keys exceed U.
-//   pass 2  (only in a workgroup with a token whose third key does not)
+//           bounds of the third exceed U.
+//   pass 2  (only in a workgroup with a token where one does not)
 //           lists every codeword with L_j <= U of those tokens: their B
 //           operands are compacted into 32-token tiles in LDS, and each wave
 //           screens a quarter of the codeword tiles against them, codebook
@@ -50,7 +51,7 @@
 // (direct-to-LDS, one __shared__ array per stage) as the A operand
 // (codewords along M).
 // Each lane thus sees the scores of ONE token for 16 codewords per tile;
-// the fold of one tile into (m1, m2, m3) overlaps the matrix products of the
+// the fold of one tile into its two smallest keys overlaps the matrix products of the
 // next.  The two lane halves that share a token merge at the end of a pass.
 #include "tn_gemm.hpp"
 
@@ -121,14 +122,16 @@ struct RqSmall {
 
 // The L rounds for the workgroup's 128 tokens (blockIdx.x), given each
 // lane's fp32 residual R_0 = Z0 (columns 16 s + 8 (lane / 32) + 0..7 of
-// token 32 wave + lane % 32; zeros past T).  s0, s1, s2: three stage
+// token 32 wave + lane % 32; zeros past T) and the rounds' scales (lane l:
+// round l, l < RQ_LMAX; loaded before the residual is there, because a load
+// at the start of a round would be waited for).  s0, s1, s2: three stage
 // buffers of at least sizeof(RqStage<R>) bytes, each its own __shared__
 // object (stage 2 also holds the residuals of the tokens being rescored).
 // No load may be in flight on entry and the workgroup must have passed a
 // barrier after its last use of the buffers.
 template <int R>
 __device__ __forceinline__ void rvq_rounds(const RvqArgs& a, bf16_t* s0, bf16_t* s1, bf16_t* s2, RqSmall& sm,
-                                           float (&res)[R / 16][8]) {
+                                           float (&res)[R / 16][8], float scales) {
   constexpr int NK16 = R / 16;                     // k-steps of the coordinates
   constexpr int CPR = (R + 16) / 8;                // 16 B chunks per codeword row
   constexpr int LOADS = rq_blocks<R>();            // DMA blocks per wave per stage
@@ -184,7 +187,7 @@ __device__ __forceinline__ void rvq_rounds(const RvqArgs& a, bf16_t* s0, bf16_t*
     // error ||R_l - R~_l||^2 with -2 R~ = fp16(-2 R) (the difference is exact
     // in fp32; a coordinate past fp16's range makes it infinite, see `hard`).
     // Coordinates stay scaled in this block only: res keeps the fp32 residual.
-    const float scale = a.scale[l], m2s = -2.f * scale;
+    const float m2s = -2.f * __uint_as_float((uint32_t)__builtin_amdgcn_readlane(__float_as_int(scales), l));
     uint4 rb[NK16];
     float rn2 = 0.f, er2 = 0.f;
 #pragma unroll
@@ -330,10 +333,10 @@ __device__ __forceinline__ void rvq_rounds(const RvqArgs& a, bf16_t* s0, bf16_t*
     // (the screen subtracts that codeword's own error bound), and s_j1 <= U =
     // L_j1 + (RVQ_SUB_FACTOR + 1) Delta_j1 for the smallest key j1 (of equal
     // keys, half 0's), so only codewords with L_j <= U can be nearest.
-    //  pass 1: per lane the three smallest keys and the positions of the first
-    //    two; a token is final when its second key exceeds U; its listed keys
-    //    are all its candidates when the third keys of both halves exceed U;
-    //  pass 2 (only in a workgroup with a token whose third key does not):
+    //  pass 1: per lane the two smallest keys with their positions and a bound
+    //    of the third; a token is final when its second key exceeds U; its kept
+    //    keys are all its candidates when the bounds of both halves exceed U;
+    //  pass 2 (only in a workgroup with a token where one does not):
     //    every key <= U of those tokens listed (the tokens compacted); the
     //    candidates are rescored exactly in fp32.
     const float* n2l = a.meta + (int64_t)l * nchunks * 64;
@@ -344,29 +347,35 @@ __device__ __forceinline__ void rvq_rounds(const RvqArgs& a, bf16_t* s0, bf16_t*
       return (cco * e2l[jj] + bco * (sqrtf(n2) * (1.0f + 1.0f / 32768.0f)) + rvq_margin_k2(R) * n2) * 1.0002f +
              1e-30f;
     };
-    // ---- pass 1: the three smallest keys per lane (slot tags) and the tiles
-    // of the first two
+    // ---- pass 1: the two smallest keys per lane (slot tags) with their tiles
+    // and a bound of the third
     int j1;
     float thr;
     bool open, need2;  // not final; its candidates have to be listed by pass 2
     {
-      float m1 = INFINITY, m2 = INFINITY, m3 = INFINITY, m1_in = INFINITY, m2_in = INFINITY;
+      // t1 <= t2: the tile's smallest keys; m1 <= m2: the lane's so far; m3:
+      // a lower bound of every other key of the lane
+      float m1 = INFINITY, m2 = INFINITY, m3 = INFINITY, t1 = INFINITY, t2 = INFINITY;
       int tile1 = 0, tile2 = 0;
-      pass([&]() { m1_in = m1; m2_in = m2; },
+      pass([&]() { t1 = t2 = INFINITY; },
            [&](const f32x16_t& acc, int, auto ec) {
              constexpr int E = decltype(ec)::value;
              const float key = rq_tag_slot(acc[E], E);
-             m3 = __builtin_amdgcn_fmed3f(m2, m3, key);
-             m2 = __builtin_amdgcn_fmed3f(m1, m2, key);
-             m1 = __builtin_amdgcn_fmed3f(m1, key, -3.40282347e38f);  // min for finite keys
+             t2 = __builtin_amdgcn_fmed3f(t1, t2, key);
+             t1 = __builtin_amdgcn_fmed3f(t1, key, -3.40282347e38f);  // min for finite keys
            },
            [&](int tile) {
-             // a new smallest key displaces the old one to second place or
-             // has a second of its own tile beside it (where both are equal,
-             // so is the third, and the token is not decided from keys)
-             const bool n1 = m1 < m1_in;
-             tile2 = n1 ? (m2 == m1_in ? tile1 : tile) : (m2 < m2_in ? tile : tile2);
+             // The two smallest of the four; the rest is at least max(m2, t1)
+             // or t2, and so is the tile's unseen third key at least t2 (two
+             // kept keys of one half tile leave the token to pass 2).  Of
+             // equal keys the earlier tile's is the smallest.
+             const bool n1 = t1 < m1;
+             const float hi = fmaxf(m1, t1), s2 = fminf(fminf(hi, m2), t2);
+             m3 = fminf(fminf(m3, fmaxf(m2, t1)), t2);
+             tile2 = n1 ? (s2 == m1 ? tile1 : tile) : (s2 < m2 ? tile : tile2);
              tile1 = n1 ? tile : tile1;
+             m1 = fminf(m1, t1);
+             m2 = s2;
            },
            true);
       const float o1 = __shfl_xor(m1, 32, WAVE), o2 = __shfl_xor(m2, 32, WAVE), o3 = __shfl_xor(m3, 32, WAVE);
@@ -701,6 +710,7 @@ __global__ __launch_bounds__(RQ_THREADS) __attribute__((amdgpu_waves_per_eu(1, 1
   __shared__ RqSmall sm;
   const int lane = threadIdx.x & 63, half = lane >> 5;
   const int t = blockIdx.x * RQ_TOK + (threadIdx.x >> 6) * 32 + (lane & 31);
+  const float scales = a.scale[lane & (RQ_LMAX - 1)];
   float res[R / 16][8];
 #pragma unroll
   for (int s = 0; s < R / 16; ++s) {
@@ -713,7 +723,7 @@ __global__ __launch_bounds__(RQ_THREADS) __attribute__((amdgpu_waves_per_eu(1, 1
     res[s][0] = z0.x; res[s][1] = z0.y; res[s][2] = z0.z; res[s][3] = z0.w;
     res[s][4] = z1.x; res[s][5] = z1.y; res[s][6] = z1.z; res[s][7] = z1.w;
   }
-  rvq_rounds<R>(a, S0.c, S1.c, S2.c, sm, res);
+  rvq_rounds<R>(a, S0.c, S1.c, S2.c, sm, res, scales);
 #endif
 }
 
@@ -746,6 +756,7 @@ __global__ __launch_bounds__(RQ_THREADS) __attribute__((amdgpu_waves_per_eu(1, 1
                     : t < 2 * ROWS ? lds_addr(&S1) + (uint32_t)(t - ROWS) * 1024u
                                    : lds_addr(S2buf) + (uint32_t)(t - 2 * ROWS) * 1024u;
   };
+  const float scales = a.scale[lane & (RQ_LMAX - 1)];  // here long before it is used
   tn_mainloop<R, 3, FULLK, false>(g, 1, S0.a, S0.w, S1.a, S1.w, S2buf, S2buf + GM * GK,
                            [&](f32x16_t (&acc)[2][R / 64], int) {
                              __syncthreads();  // every wave is done reading the stages
@@ -798,7 +809,7 @@ __global__ __launch_bounds__(RQ_THREADS) __attribute__((amdgpu_waves_per_eu(1, 1
     }
   }
   __syncthreads();  // the stages are free for the codebook
-  rvq_rounds<R>(a, S0.a, S1.a, S2buf, sm, res);
+  rvq_rounds<R>(a, S0.a, S1.a, S2buf, sm, res, scales);
 #endif
 }
 

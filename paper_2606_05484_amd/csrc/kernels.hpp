@@ -152,8 +152,6 @@ hipError_t launch_transpose_into(const void* src, int src_f32, int rows, int col
 // Cb[l][j][r+6:r+16] = 0.  meta[0][l][chunk][64]: ||C'_j||^2 in fp32 per
 // 64-codeword chunk, meta[1][l][chunk][64]: ||C'_j - fp16(C'_j)|| rounded up
 // (zero past K).
-hipError_t launch_prep_codebook(const float* C, int L, int K, int r, bf16_t* Cb, float* meta, float* scale,
-                                hipStream_t s);
 inline int64_t rvq_meta_floats(int L, int K) { return 2 * (int64_t)L * ((K + 63) / 64) * 64; }
 __host__ __device__ constexpr int rvq_cb_cols(int r) { return r + 16; }
 
@@ -217,7 +215,7 @@ struct RvqArgs {
   const bf16_t* Cb;    // [L,K,r+16] fp16 screening copy with the split norms (rvq_cb_cols)
   const float* C;      // [L,K,r] fp32 codebooks
   const float* meta;   // [2][L][ceil(K/64)][64]: ||C'_j||^2, ||C'_j - fp16(C'_j)|| (rvq_meta_floats)
-  const float* scale;  // [L] the rounds' powers of two
+  const float* scale;  // [8] the rounds' powers of two (entries past L are read, not used)
   int T, r, L, K;
   void* codes; int code_bytes;  // [T,L]
   int* stats;          // [8] optional counters, may be null: tokens rescored, their candidates,
