@@ -26,10 +26,10 @@ FLAGS = ["--offload-arch=%s" % ARCH, "-O3", "-std=c++17", "-fPIC", "-Wall", "-Wn
          "-I", os.path.join(ROOT, "include")]
 
 
-# Per-file flags: the RVQ kernel keeps its accumulators in ordinary VGPRs
-# (its score fold reads every accumulator element; the AGPR form would add
+# Per-file flags: the RVQ kernels keep their accumulators in ordinary VGPRs
+# (their score folds read every accumulator element; the AGPR form would add
 # a copy per element).
-EXTRA = {"k_rvq.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form=1"]}
+EXTRA = {f: ["-mllvm", "-amdgpu-mfma-vgpr-form=1"] for f in ("k_rvq.hip", "k_grvq.hip")}
 
 
 def _compile(src):
