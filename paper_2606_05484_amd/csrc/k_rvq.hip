@@ -31,15 +31,15 @@
 //           operands are compacted into 32-token tiles in LDS, and each wave
 //           screens a quarter of the codeword tiles against them, codebook
 //           fragments read straight from the L2-resident screening copy.
-// At the 1B-model boundary (T = 32768, r = 256, K = 1024, codewords drawn
-// from the residuals, a decaying spectrum) the bf16 screen left 34 % of the
-// token-rounds open, every workgroup in pass 2 and some tokens to a rescan of
-// the whole codebook: 420-510 us per call.  With fp16 7 % are open and a
-// sixth of the workgroup-rounds list: 130 us.
 //   rescore the listed candidates exactly in fp32 as sum_c (R_c - C_jc)^2:
 //           per wave a batch of up to 8 open tokens, their residual rows
 //           staged in LDS, 8 (token, codeword) pairs per step with coalesced
 //           codeword rows and one cross-lane reduction for all 8.
+// At the 1B-model boundary (T = 32768, r = 256, K = 1024, codewords drawn
+// from the residuals, a decaying spectrum) the bf16 screen left 34 % of the
+// token-rounds open, every workgroup in pass 2 and some tokens to a rescan of
+// the whole codebook: 420-510 us per call.  With fp16 7 % are open and a
+// sixth of the workgroup-rounds list: 122-128 us.
 // The fp32 residual stays in registers across rounds, updated as
 // R_{l+1} = R_l - C_l[code_l]; the rescoring reads it from there (through
 // LDS rows), so screening and rescoring see the same R.

@@ -437,7 +437,7 @@ extern "C" int mapl_encode(const mapl_codec_desc* desc, const void* X, const int
 
   if (D.x_dtype == MAPL_BF16) {
     // one launch: Wt = [U~^T | -(B_s U~)^T] (or the coordinate anchor's
-    // -B_s^T), and the bf16 codebook copy with its norms
+    // -B_s^T), and the fp16 screening codebook with its norms
     bf16_t* Wt = at<bf16_t>(ws, Lo.w);
     bf16_t* Cb = D.L > 0 ? at<bf16_t>(ws, Lo.cb) : nullptr;
     float* meta = D.L > 0 ? at<float>(ws, Lo.cn2) : nullptr;
