@@ -212,8 +212,9 @@ def _short(sym):
 
 def _counter_table(d, order, agg):
     """Mean of every counter of one rocprofv3 --pmc run per chain kernel; with
-    MfmaFlopsBF16 / MfmaFlopsF32 also the matrix rate they imply over the
-    kernel's trace duration, against the dense MFMA peak of its type."""
+    MfmaFlopsBF16, MfmaFlopsF16 (one rate, their sum) or MfmaFlopsF32 also the
+    matrix rate they imply over the kernel's trace duration, against the dense
+    MFMA peak of its type."""
     disp = _dispatches(d, "_counter_collection.csv")
     named = _chain_map(disp, order, len([x for x in disp if "mapl::" in x[1]]) // len(order))
     acc = {}
@@ -221,11 +222,11 @@ def _counter_table(d, order, agg):
         for c, v in e["ctr"].items():
             acc.setdefault(name, {}).setdefault(c, []).append(v)
     ctrs = sorted({c for v in acc.values() for c in v})
-    rate = [c for c in ("MfmaFlopsBF16", "MfmaFlopsF32") if c in ctrs]
+    rate = ["MfmaFlopsBF16", "MfmaFlopsF16", "MfmaFlopsF32"] if any(c.startswith("MfmaFlops") for c in ctrs) else []
     out = ["", "# rocprofv3 --pmc %s (mean per launch; percentages as rocprofv3 derives them)" % " ".join(ctrs)]
     if rate:
         out.append("# TFLOP/s = counted matrix flops over the kernel's trace duration; frac against the dense "
-                   "peak of that type (bf16 2516.6, fp32 157.3)")
+                   "peak of that type (16-bit 2516.6, fp32 157.3)")
     hdr = "%-24s" % "kernel" + "".join(" %16s" % c for c in ctrs) + ("  %9s %6s" % ("TFLOP/s", "frac") if rate else "")
     out.append(hdr)
     for name in order:
@@ -233,11 +234,11 @@ def _counter_table(d, order, agg):
         row = "%-24s" % name + "".join(" %16.4g" % np.mean(v[c]) if c in v else " %16s" % "-" for c in ctrs)
         if rate:
             us = agg[name][2] / agg[name][1]
-            fl = {c: np.mean(v[c]) for c in rate if c in v}
-            best = max(fl, key=fl.get) if fl else None
-            if best and fl[best] > 0:
-                tf = fl[best] / us / 1e6
-                row += "  %9.1f %6.3f" % (tf, tf * 1e12 / (PEAK_BF16 if best == "MfmaFlopsBF16" else PEAK_F32))
+            f16 = sum(np.mean(v[c]) for c in rate[:-1] if c in v)
+            f32 = np.mean(v[rate[-1]]) if rate[-1] in v else 0.0
+            if max(f16, f32) > 0:
+                tf = max(f16, f32) / us / 1e6
+                row += "  %9.1f %6.3f" % (tf, tf * 1e12 / (PEAK_BF16 if f16 > f32 else PEAK_F32))
             else:
                 row += "  %9s %6s" % ("-", "-")
         out.append(row)
