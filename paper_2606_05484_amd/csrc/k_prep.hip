@@ -79,9 +79,11 @@ __device__ __forceinline__ float rvq_round_scale(const float* __restrict__ C, in
   __syncthreads();
   m = fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3]));
   if (!(m > 0.f)) return 1.f;
-  // exponent field e of m: 2^(5 - (e - 127)), kept a normal number
+  // exponent field e of m: 2^(5 - (e - 127)), kept a normal number, and so
+  // that the rounds' -2 times it is finite too (an infinite factor would make
+  // NaN of a residual coordinate that is exactly zero)
   const int e = (int)(__float_as_uint(m) >> 23);
-  return __uint_as_float((uint32_t)min(max(127 + 5 + 127 - e, 1), 254) << 23);
+  return __uint_as_float((uint32_t)min(max(127 + 5 + 127 - e, 1), 253) << 23);
 }
 
 // One wave per (stage, codeword slot of a 64-codeword chunk): the fp16 copy

@@ -73,6 +73,30 @@ def test_codebook_scale(r, q):
 
 @pytest.mark.gpu
 @pytest.mark.parametrize("r", [64, 128, 256])
+@pytest.mark.parametrize("q", [-149, -125, -121])
+def test_sampled_coordinates_near_zero(r, q):
+    """The codewords' coordinates that the round's scale is taken from (four of
+    each, see rvq_round_scale) at 2^q, the others ordinary, and every token
+    with an exactly zero coordinate: the scale ends at its largest power of
+    two, the bounds are not finite, and the codes are the exact ones."""
+    x = synth.codec_inputs(None, seed=34, **dict(SMALL, r=r, L=1))
+    x["U"] = x["U"].copy()
+    x["U"][:, 3] = 0.0
+    C = stress_codebooks(x, 11)
+    for j in range(C.shape[1]):
+        c0 = 4 * ((j * 17) % (r // 4))
+        C[0, j, c0:c0 + 4] = np.float32(2.0 ** q)
+    Z0 = ocodec.project(f64(x, "X"), x["ids"], x["U"], f64(x, "A"), f64(x, "B"), "ambient", "bf16")
+    assert (Z0[:, 3] == 0).all()
+    ref, gap, _ = ocodec.rvq_encode(Z0, C)
+    assert (ref != 0).mean() > 0.5
+    bad, ex = compare_codes(_encode(x, C), ref, gap)
+    print("mismatched", bad, "exempt", ex)
+    assert bad == 0
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("r", [64, 128, 256])
 def test_out_of_range_token_and_codeword(r):
     """A token 2^13 times the others and a codeword on it whose sampled
     coordinates are zero, so the round's scale does not see it: the codeword
