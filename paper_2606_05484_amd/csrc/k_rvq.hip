@@ -185,29 +185,52 @@ __device__ __forceinline__ void rvq_rounds(const RvqArgs& a, bf16_t* s0, bf16_t*
     // In the round's scaled units (the residual times the codebook's power
     // of two): fp16(-2 R_l) in B-fragment layout, ||R_l||^2 and the rounding
     // error ||R_l - R~_l||^2 with -2 R~ = fp16(-2 R) (the difference is exact
-    // in fp32; a coordinate past fp16's range makes it infinite, see `hard`).
-    // Coordinates stay scaled in this block only: res keeps the fp32 residual.
+    // in fp32).  Coordinates stay scaled in this block only: res keeps the
+    // fp32 residual.
     const float m2s = -2.f * __uint_as_float((uint32_t)__builtin_amdgcn_readlane(__float_as_int(scales), l));
     uint4 rb[NK16];
-    float rn2 = 0.f, er2 = 0.f;
+    float rn2, er2;
+    auto operand = [&](float f) {
+      rn2 = er2 = 0.f;
 #pragma unroll
-    for (int s = 0; s < NK16; ++s) {
-      const float* v = res[s];
-      uint32_t w[4];
+      for (int s = 0; s < NK16; ++s) {
+        const float* v = res[s];
+        uint32_t w[4];
 #pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const float x0 = m2s * v[2 * e], x1 = m2s * v[2 * e + 1];
-        w[e] = pack_h2(x0, x1);
-        const float d0 = x0 - h2f(w[e] & 0xFFFFu), d1 = x1 - h2f(w[e] >> 16);
-        rn2 = fmaf(x0, x0, rn2);
-        rn2 = fmaf(x1, x1, rn2);
-        er2 = fmaf(d0, d0, er2);
-        er2 = fmaf(d1, d1, er2);
+        for (int e = 0; e < 4; ++e) {
+          const float x0 = f * v[2 * e], x1 = f * v[2 * e + 1];
+          w[e] = pack_h2(x0, x1);
+          const float d0 = x0 - h2f(w[e] & 0xFFFFu), d1 = x1 - h2f(w[e] >> 16);
+          rn2 = fmaf(x0, x0, rn2);
+          rn2 = fmaf(x1, x1, rn2);
+          er2 = fmaf(d0, d0, er2);
+          er2 = fmaf(d1, d1, er2);
+        }
+        rb[s] = make_uint4(w[0], w[1], w[2], w[3]);
       }
-      rb[s] = make_uint4(w[0], w[1], w[2], w[3]);
+      rn2 += __shfl_xor(rn2, 32, WAVE);
+      er2 += __shfl_xor(er2, 32, WAVE);
+    };
+    operand(m2s);
+    // A coordinate past fp16's range makes er2 infinite.  Such a token's whole
+    // operand, norm step included, takes a power of two tsc of its own: its
+    // scores and their bounds are all tsc times what they were, so its
+    // decisions are the same.  (Without it every such token was scored
+    // against the whole codebook: T = 8192, K = 1024, codewords 2^-12 of the
+    // residuals: 10.9 ms.)  Up to 2^49 only; larger ones are `hard`, see
+    // below.
+    float tsc = 1.f;
+    if (__any(!(er2 < INFINITY))) {
+      float mx = 0.f;
+#pragma unroll
+      for (int s = 0; s < NK16; ++s)
+#pragma unroll
+        for (int e = 0; e < 8; ++e) mx = fmaxf(mx, fabsf(res[s][e]));
+      mx = fmaxf(mx, __shfl_xor(mx, 32, WAVE)) * fabsf(m2s);
+      // 2^14 <= tsc mx < 2^15
+      if (mx >= 65504.f && mx < 0x1p49f) tsc = __uint_as_float((127u + 14u + 127u - (__float_as_uint(mx) >> 23)) << 23);
+      operand(m2s * tsc);
     }
-    rn2 += __shfl_xor(rn2, 32, WAVE);
-    er2 += __shfl_xor(er2, 32, WAVE);
     // norms of R, half those of -2 R, rounded up (each sum carries at most R
     // ulps of accumulation error)
     const float rnorm = 0.5f * sqrtf(rn2) * (1.0f + 1.0f / 32768.0f);
@@ -231,13 +254,14 @@ __device__ __forceinline__ void rvq_rounds(const RvqArgs& a, bf16_t* s0, bf16_t*
     // one fragment read per product.
     constexpr int P = NK16 + 1;
     constexpr int FPS = (16 + P - 1) / P;  // scores folded per product step
-    // second operand of the norm step: ones in k = 0..2 (the reduced norm's
+    // second operand of the norm step: ones (tsc) in k = 0..2 (the reduced norm's
     // pieces), -b in k = 3, 4 (times the norm's pieces) and -c in k = 5
     // (times the rounding-error norm) of the block: the screen yields the
     // lower bound L_j of each codeword's score
     const uint32_t bbits = bf16_up(bco * RVQ_K1_SLACK) | 0x8000u;
     const uint32_t cbits = bf16_up(cco * RVQ_K1_SLACK) | 0x8000u;
-    const uint4 rbn = half == 0 ? make_uint4(0x3F803F80u, 0x3F80u | (bbits << 16), bbits | (cbits << 16), 0u)
+    const uint32_t ones = __float_as_uint(tsc) >> 16;  // bf16(tsc), exact
+    const uint4 rbn = half == 0 ? make_uint4(ones | ones << 16, ones | (bbits << 16), bbits | (cbits << 16), 0u)
                                 : make_uint4(0u, 0u, 0u, 0u);
     auto pass = [&](auto&& fbegin, auto&& fscore, auto&& fend, bool first) {
       if (!first) {
@@ -344,7 +368,7 @@ __device__ __forceinline__ void rvq_rounds(const RvqArgs& a, bf16_t* s0, bf16_t*
     auto margin = [&](int j) {  // Delta_j, rounded up
       const int jj = min(max(j, 0), nchunks * 64 - 1);
       const float n2 = n2l[jj];
-      return (cco * e2l[jj] + bco * (sqrtf(n2) * (1.0f + 1.0f / 32768.0f)) + rvq_margin_k2(R) * n2) * 1.0002f +
+      return (cco * e2l[jj] + bco * (sqrtf(n2) * (1.0f + 1.0f / 32768.0f)) + rvq_margin_k2(R) * (tsc * n2)) * 1.0002f +
              1e-30f;
     };
     // ---- pass 1: the two smallest keys per lane (slot tags) with their tiles
@@ -389,7 +413,7 @@ __device__ __forceinline__ void rvq_rounds(const RvqArgs& a, bf16_t* s0, bf16_t*
       // bounds are not finite): every codeword is a candidate.  A NaN residual
       // has no nearest codeword and takes 0.
       const bool nan = rn2 != rn2;
-      const bool hard = !(rn2 < 1e30f) || !(fabsf(thr) < 1e37f);
+      const bool hard = !(rn2 < 1e30f) || !(fabsf(thr) < 1e37f * tsc);
       open = valid && !nan && (hard || !(k2 > thr));
       j1 = nan ? 0 : j1;
       // a token whose third keys exceed U is rescored from its listed first

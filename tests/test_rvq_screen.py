@@ -120,6 +120,38 @@ def test_out_of_range_token_and_codeword(r):
 
 @pytest.mark.gpu
 @pytest.mark.parametrize("r", [64, 128, 256])
+@pytest.mark.parametrize("q,part", [(-10, 1.0), (-12, 1.0), (-12, 0.3), (-30, 1.0)])
+def test_tokens_far_above_the_codebook(r, q, part):
+    """Codebooks 2^q of the residuals (part of the tokens; the others' X is
+    scaled down to match): fp16(-2R) overflows in the round's units, the
+    tokens take a power of two of their own, and are screened like others: no
+    list overflows.  Codes count where the distances differ by more than fp32
+    resolves (2e-6 of ||R||^2; at 2^-30 none does, and the first codeword of
+    the equal fp32 distances is not determined by the float64 oracle)."""
+    x = synth.codec_inputs(None, seed=35, **dict(SMALL, r=r, k=0))
+    C = (stress_codebooks(x, 12) * np.float32(2.0 ** q)).astype(np.float32)
+    C[:, 0] = C[:, 1] * np.float32(0.5)  # no zero codeword: the screen's scale is that of the others
+    near = np.random.default_rng(5).uniform(size=x["T"]) >= part
+    X = x["X"].copy()
+    X[near] = np.where((X[near] & 0x7F80) > (-q << 7), X[near] - (-q << 7), 0)  # bf16 bits: the exponent down by -q
+    x["X"] = X
+    Z0 = ocodec.project(f64(x, "X"), x["ids"], x["U"], f64(x, "A"), f64(x, "B"), "ambient", "bf16")
+    ref, gap, _ = ocodec.rvq_encode(Z0, C)
+    mapl.profile(2)
+    try:
+        got = _encode(x, C)
+        stats = mapl.profile_report()
+    finally:
+        mapl.profile(0)
+    exempt = (gap < 2e-6).any(1)
+    bad = int(((got != ref).any(1) & ~exempt).sum())
+    print("mismatched", bad, "exempt", int(exempt.sum()), {k: v[0] for k, v in stats.items() if k.startswith("rvq:")})
+    assert bad == 0 and (q < -20 or exempt.mean() < 0.5)
+    assert stats["rvq:list_overflows"][0] == 0
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("r", [64, 128, 256])
 @pytest.mark.parametrize("rows", [(0, 1), (0, 4), (0, 1, 2), (3, 8, 40), (0, 1, 4, 5), (0, 1, 4, 5, 8, 12),
                                   tuple(range(40, 60))])
 def test_near_ties_by_lane_half(r, rows):
