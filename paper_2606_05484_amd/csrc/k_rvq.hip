@@ -102,6 +102,20 @@ __device__ __forceinline__ f32x16_t rq_mfma(const uint4& a, const uint4& b, f32x
     return mfma32x32x16h(a, b, c);
 }
 
+// Minima and maxima of keys, one operation each: fminf takes one more per
+// operand, because keys come from integer operations and could be signalling
+// NaN as far as the compiler knows.  A quiet NaN yields the other operand.
+__device__ __forceinline__ float rq_max(float a, float b) {
+  float r;
+  asm("v_max_f32 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
+  return r;
+}
+__device__ __forceinline__ float rq_min3(float a, float b, float c) {
+  float r;
+  asm("v_min3_f32 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));
+  return r;
+}
+
 // A score tagged in its low 4 mantissa bits with its slot among the lane's
 // 16 scores of a tile (inline constants, one operation): a plain float min /
 // med3 then also carries the slot.  The tag moves a score by less than
@@ -248,8 +262,10 @@ __device__ __forceinline__ void rvq_rounds(const RvqArgs& a, bf16_t* s0, bf16_t*
     //     of the fold of the previous chunk's tile 1
     //   tile 1 products, each followed by a later fragment read and a share
     //     of the fold of tile 0
-    // Reads of an invalid second tile (K % 64 == 32) hit zero-filled rows and
-    // are discarded.
+    // The last chunk's second tile may not exist (K % 64 == 32): its rows are
+    // zero-filled and its scores, the last to be folded, are left out.  (The
+    // loop has no branch between the products: the compiler would move them
+    // past the folds.)
     // Products per tile: the norm step, then the NK16 coordinate k-steps;
     // one fragment read per product.
     constexpr int P = NK16 + 1;
@@ -285,7 +301,6 @@ __device__ __forceinline__ void rvq_rounds(const RvqArgs& a, bf16_t* s0, bf16_t*
         __builtin_amdgcn_s_barrier();
         if (q + 2 < total) issue(q + 2, nc);
         if (q >= nchunks) return;
-        const bool t1ok = q * RQ_CW + 32 < a.K;
         // rows lane % 32 of a tile, 16 B chunk 2s + lane / 32 (s = NK16: the
         // norm columns)
         const uint32_t cbase = lds_addr(sc) + (lane & 31) * RB + half * 16;
@@ -310,8 +325,6 @@ __device__ __forceinline__ void rvq_rounds(const RvqArgs& a, bf16_t* s0, bf16_t*
             return rb[S - 1];
         };
         static_for<0, W>([&](auto pc) { read(pc); });
-        // an invalid second tile (K % 64 == 32) reads zero rows; its
-        // products are computed and discarded
         f32x16_t acc0 = f32x16_t{}, acc1 = f32x16_t{};
         static_for<0, NP2>([&](auto pc) {
           constexpr int PI = decltype(pc)::value, CT = PI / P, S = PI % P;
@@ -336,21 +349,15 @@ __device__ __forceinline__ void rvq_rounds(const RvqArgs& a, bf16_t* s0, bf16_t*
           __builtin_amdgcn_sched_barrier(0);
         });
         fend(2 * q);
-        if (t1ok) {
-          pend = acc1;
-          pend_tile = 2 * q + 1;
-        } else {
-#pragma unroll
-          for (int e = 0; e < 16; ++e) pend[e] = 3.0e38f;
-          pend_tile = -1;
-        }
+        pend = acc1;
+        pend_tile = 2 * q + 1;
       };
       for (int q = 0; q < total; q += 3) {
         stage(q, s0, s2);
         stage(q + 1, s1, s0);
         stage(q + 2, s2, s1);
       }
-      fold_all(pend, pend_tile);
+      if (a.K % RQ_CW == 0) fold_all(pend, pend_tile);
     };
 
     // Decision.  Each key is a lower bound L_j of its codeword's exact score
@@ -379,26 +386,34 @@ __device__ __forceinline__ void rvq_rounds(const RvqArgs& a, bf16_t* s0, bf16_t*
     {
       // t1 <= t2: the tile's smallest keys; m1 <= m2: the lane's so far; m3:
       // a lower bound of every other key of the lane
-      float m1 = INFINITY, m2 = INFINITY, m3 = INFINITY, t1 = INFINITY, t2 = INFINITY;
+      float m1 = INFINITY, m2 = INFINITY, m3 = INFINITY, t1, t2;
       int tile1 = 0, tile2 = 0;
-      pass([&]() { t1 = t2 = INFINITY; },
+      pass([]() {},
            [&](const f32x16_t& acc, int, auto ec) {
              constexpr int E = decltype(ec)::value;
              const float key = rq_tag_slot(acc[E], E);
-             t2 = __builtin_amdgcn_fmed3f(t1, t2, key);
-             t1 = __builtin_amdgcn_fmed3f(t1, key, -3.40282347e38f);  // min for finite keys
+             if constexpr (E == 0) {
+               t1 = key;
+             } else {
+               t2 = E == 1 ? rq_max(t1, key) : __builtin_amdgcn_fmed3f(t1, t2, key);
+               t1 = __builtin_amdgcn_fmed3f(t1, key, -3.40282347e38f);  // min for finite keys
+             }
            },
            [&](int tile) {
              // The two smallest of the four; the rest is at least max(m2, t1)
              // or t2, and so is the tile's unseen third key at least t2 (two
              // kept keys of one half tile leave the token to pass 2).  Of
-             // equal keys the earlier tile's is the smallest.
+             // equal keys the earlier tile's is the smallest.  Selects in this
+             // order, because the compiler made branches of nested ones, which
+             // cut the products in two (r = 64, K = 4096, L = 2 at 8192
+             // tokens: 105.6 us a call, 89.3 so).
              const bool n1 = t1 < m1;
-             const float hi = fmaxf(m1, t1), s2 = fminf(fminf(hi, m2), t2);
-             m3 = fminf(fminf(m3, fmaxf(m2, t1)), t2);
-             tile2 = n1 ? (s2 == m1 ? tile1 : tile) : (s2 < m2 ? tile : tile2);
+             const float s1 = n1 ? t1 : m1, s2 = rq_min3(rq_max(m1, t1), m2, t2);
+             m3 = rq_min3(m3, rq_max(m2, t1), t2);
+             tile2 = s2 < m2 ? tile : tile2;
+             tile2 = n1 & (s2 == m1) ? tile1 : tile2;
              tile1 = n1 ? tile : tile1;
-             m1 = fminf(m1, t1);
+             m1 = s1;
              m2 = s2;
            },
            true);

@@ -175,3 +175,37 @@ def test_near_ties_by_lane_half(r, rows):
     bad, ex = compare_codes(got, ref, gap)
     print("token 5", got[5], "mismatched", bad, "exempt", ex)
     assert got[5, 0] == rows[-1] and bad == 0
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("r", [64, 128, 256])
+@pytest.mark.parametrize("K", [32, 96, 160, 256])
+def test_equal_codewords_over_tiles(r, K):
+    """Every codeword two or three times, at places of the same and of
+    different slots, lane halves and 32-row tiles (K % 64 == 32 among them,
+    whose last chunk has one tile): equal keys meet in every merge, and the
+    lowest index is the code."""
+    x = synth.codec_inputs(None, seed=36, **dict(SMALL, r=r, K=K))
+    C = stress_codebooks(x, 13)
+    rng = np.random.default_rng(K)
+    base = {s: rng.permutation(K)[:K // 3 + 1] for s in range(2)}
+    for l in range(2):
+        src = base[l][np.arange(K) % len(base[l])]
+        C[l] = C[l][src[rng.permutation(K)]]
+        for j in range(0, K - 32, 7):  # the same slot of the next tile
+            C[l, j + 32] = C[l, j]
+    Z0 = ocodec.project(f64(x, "X"), x["ids"], x["U"], f64(x, "A"), f64(x, "B"), "ambient", "bf16")
+    got = _encode(x, C).astype(np.int64)
+    R = Z0.copy()
+    open_ = np.ones(len(R), bool)  # no near tie between different codewords so far
+    bad = 0
+    for l in range(2):
+        d = ((R[:, None, :] - C[l].astype(np.float64)[None]) ** 2).sum(-1)
+        first = np.array([np.flatnonzero((C[l] == C[l, j]).all(1))[0] for j in range(K)])
+        best = first[d.argmin(1)]
+        others = np.where(first[None] == best[:, None], np.inf, d).min(1)
+        open_ &= others - d.min(1) > 1e-4 * (R ** 2).sum(1)
+        bad += int((open_ & (got[:, l] != best)).sum())
+        R = R - C[l].astype(np.float64)[best]
+    print("mismatched", bad, "compared", int(open_.sum()))
+    assert bad == 0 and open_.mean() > 0.5
