@@ -1,6 +1,6 @@
 // Batched strided fp32 GEMM:
 //   C[b](m,n) = alpha * sum_k A[b](m,k) B[b](k,n) + beta * Cin[b](m,n)
-// on the fp32 matrix units (v_mfma_f32_32x32x2_f32) or, with GEMM_SPLIT_F16, as
+// (optionally with a second sum whose A rows are gathered by token id) on the fp32 matrix units (v_mfma_f32_32x32x2_f32) or, with GEMM_SPLIT_F16, as
 // products of fp16 pieces on the 16-bit matrix units (k_gemm_x3).  Products
 // with few output tiles, or with strides that the vector loads here do not
 // take, run in k_gemm_f32s.hip.
@@ -19,13 +19,21 @@ constexpr int GF_THREADS = 256;
 // 32 at a time with 16-byte global loads into registers one stage ahead and
 // two LDS buffers, so the matrix units work on one stage while the next is
 // in flight (one barrier per stage).  A is either m-contiguous (AK = false:
-// A(m,k) at A + m + k*sAk) or k-contiguous (AK = true: A + m*sAm + k); B is
-// n-contiguous.  LDS holds both operands as k-pairs: s[k/2][m'][k%2], so the
+// A(m,k) at A + m + k*sAk) or k-contiguous (AK = true: A + m*sAm + k); B
+// likewise n-contiguous or (BK) k-contiguous.  LDS holds both operands as
+// k-pairs: s[k/2][m'][k%2], so the
 // 64 lanes of one operand read (rows m0 .. m0+31, k and k+1) touch one
 // 64-float span, every bank once; m' permutes the rows inside each group of
 // 32 so that the 8-byte stores of 32 lanes also land in distinct banks:
-// m' = m ^ ((m / 32) % 4) for tiles loaded row by row (B, m-contiguous A),
-// m' = m ^ 4 ((k / 2) % 8) for the k-contiguous A.
+// m' = m ^ ((m / 32) % 4) for tiles loaded along m (n-contiguous B,
+// m-contiguous A), m' = m ^ 4 ((k / 2) % 8) for those loaded along k.
+// SEG: after the K columns, the K2 columns of a table whose rows are gathered
+// by token id (the anchor terms of Eqs. 1 and 2) times sign2 and the
+// n-contiguous B2, into the same accumulators; under BK its B tile takes the
+// other layout with some bank conflicts (K2 is the anchor rank, a fraction of K).
+// T = 32768, d = 2048, r = 256, k = 64: the lift with its anchor as one launch
+// 395 us; in two, the lift's k-contiguous U through an unpipelined kernel,
+// 801; in k_gemm_f32s.hip 1212.
 constexpr int GV_BM = 128, GV_BN = 128, GV_BK = 32;
 
 // Tile coordinates and batch entry of a workgroup.  Workgroups are handed to
@@ -170,13 +178,14 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t gv_rsrc(const void* base, int6
   return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), 0, (int)(bytes > 0 ? bytes : 0), 0x00020000);
 }
 
-template <bool AK>
+template <bool AK, bool BK, bool SEG>
 __global__ __launch_bounds__(GF_THREADS) void k_gemm_f32v(GemmF32Args g) {
+  static_assert(AK || !SEG, "gathered rows are k-contiguous");
   __shared__ __attribute__((aligned(16))) float As[2][GV_BK / 2][GV_BM][2];
   __shared__ __attribute__((aligned(16))) float Bs[2][GV_BK / 2][GV_BN][2];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int wm = wave >> 1, wn = wave & 1;  // 2 x 2 waves, 64 x 64 each
-  const int nk = (g.K + GV_BK - 1) / GV_BK;
+  const int nk0 = (g.K + GV_BK - 1) / GV_BK, nk = nk0 + (SEG ? (g.K2 + GV_BK - 1) / GV_BK : 0);
   // the products of tile (tbm, tbn) of batch entry b over k-stages [ks0, ks1)
   auto products = [&](int b, int tbm, int tbn, int ks0, int ks1, f32x16_t (&acc)[2][2]) {
   const int m0 = tbm * GV_BM, n0 = tbn * GV_BN;
@@ -185,70 +194,89 @@ __global__ __launch_bounds__(GF_THREADS) void k_gemm_f32v(GemmF32Args g) {
       gv_rsrc((const float*)g.A + b * g.sAb,
               (AK ? (int64_t)(g.M - 1) * g.sAm + g.K : (int64_t)(g.K - 1) * g.sAk + g.M) * 4);
   const __amdgpu_buffer_rsrc_t rB =
-      gv_rsrc((const float*)g.B + b * g.sBb, ((int64_t)(g.K - 1) * g.sBk + g.N) * 4);
+      gv_rsrc((const float*)g.B + b * g.sBb,
+              (BK ? (int64_t)(g.N - 1) * g.sBn + g.K : (int64_t)(g.K - 1) * g.sBk + g.N) * 4);
+  const __amdgpu_buffer_rsrc_t rA2 = gv_rsrc(g.A2, SEG ? ((int64_t)(g.V - 1) * g.sA2 + g.K2) * 4 : 0);
+  const __amdgpu_buffer_rsrc_t rB2 = gv_rsrc(g.B2, SEG ? ((int64_t)(g.K2 - 1) * g.sB2 + g.N) * 4 : 0);
+  uint32_t row2[4];  // the thread's rows of the table
+  if constexpr (SEG) {
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      const int m = m0 + ((tid + GF_THREADS * v) >> 3);
+      row2[v] = m < g.M ? (uint32_t)clamp_id(g.ids[m], g.V) * (uint32_t)g.sA2 * 4u : GV_OOB;
+    }
+  }
 
-  // per thread and stage: B (and an m-contiguous A) as two k-pairs of four
-  // consecutive columns ([pair][row of the pair]); a k-contiguous A as four
-  // runs of four k
+  // per thread and stage: an operand contiguous along its rows as two k-pairs
+  // of four consecutive columns ([pair][row of the pair]); a k-contiguous one
+  // as four runs of four k
   raw4_t ra[4];
   raw4_t rb[4];
-  auto load = [&](int k0) {
+  auto load_m = [&](raw4_t (&r)[4], __amdgpu_buffer_rsrc_t rs, int64_t ld, int k0, int K, int c0, int C) {
 #pragma unroll
     for (int v = 0; v < 2; ++v) {
       const int idx = tid + GF_THREADS * v;  // k-pair idx / 32, columns 4 (idx % 32) .. +3
-      const int k = k0 + 2 * (idx >> 5), n = n0 + 4 * (idx & 31);
+      const int k = k0 + 2 * (idx >> 5), c = c0 + 4 * (idx & 31);
 #pragma unroll
-      for (int h = 0; h < 2; ++h) {
-        const bool ok = k + h < g.K && n < g.N;
-        rb[2 * v + h] = raw4_load(rB, ok ? (uint32_t)(((int64_t)(k + h) * g.sBk + n) * 4) : GV_OOB);
-      }
-      if constexpr (!AK) {
-        const int m = m0 + 4 * (idx & 31);
-#pragma unroll
-        for (int h = 0; h < 2; ++h) {
-          const bool ok = k + h < g.K && m < g.M;
-          ra[2 * v + h] = raw4_load(rA, ok ? (uint32_t)(((int64_t)(k + h) * g.sAk + m) * 4) : GV_OOB);
-        }
-      }
-    }
-    if constexpr (AK) {
-#pragma unroll
-      for (int v = 0; v < 4; ++v) {
-        const int idx = tid + GF_THREADS * v;  // m = idx / 8, k = 4 (idx % 8) .. +3
-        const int m = m0 + (idx >> 3), k = k0 + 4 * (idx & 7);
-        const bool ok = m < g.M && k < g.K;
-        ra[v] = raw4_load(rA, ok ? (uint32_t)(((int64_t)m * g.sAm + k) * 4) : GV_OOB);
-      }
+      for (int h = 0; h < 2; ++h)
+        r[2 * v + h] = raw4_load(rs, k + h < K && c < C ? (uint32_t)(((int64_t)(k + h) * ld + c) * 4) : GV_OOB);
     }
   };
-  auto store = [&](int buf) {
+  auto load_k = [&](raw4_t (&r)[4], __amdgpu_buffer_rsrc_t rs, int64_t ld, int k0, int K, int c0, int C) {
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      const int idx = tid + GF_THREADS * v;  // row idx / 8, k = 4 (idx % 8) .. +3
+      const int c = c0 + (idx >> 3), k = k0 + 4 * (idx & 7);
+      r[v] = raw4_load(rs, c < C && k < K ? (uint32_t)(((int64_t)c * ld + k) * 4) : GV_OOB);
+    }
+  };
+  auto load = [&](int it) {
+    if (SEG && it >= nk0) {
+      const int k0 = (it - nk0) * GV_BK, k = k0 + 4 * (tid & 7);
+      load_m(rb, rB2, g.sB2, k0, g.K2, n0, g.N);
+#pragma unroll
+      for (int v = 0; v < 4; ++v) ra[v] = raw4_load(rA2, row2[v] != GV_OOB && k < g.K2 ? row2[v] + 4u * k : GV_OOB);
+      return;
+    }
+    if constexpr (BK) load_k(rb, rB, g.sBn, it * GV_BK, g.K, n0, g.N);
+    else load_m(rb, rB, g.sBk, it * GV_BK, g.K, n0, g.N);
+    if constexpr (AK) load_k(ra, rA, g.sAm, it * GV_BK, g.K, m0, g.M);
+    else load_m(ra, rA, g.sAk, it * GV_BK, g.K, m0, g.M);
+  };
+  // columns 4 (idx % 32) .. +3 of a k-pair; KL: into the layout of k-contiguous tiles
+  auto store_m = [&](float (*s)[128][2], const raw4_t (&r)[4], auto kl) {
+    constexpr bool KL = decltype(kl)::value;
 #pragma unroll
     for (int v = 0; v < 2; ++v) {
       const int idx = tid + GF_THREADS * v;
-      const int kp = idx >> 5, c4 = 4 * (idx & 31), sw = (idx & 31) >> 3;
-      const float4 r0 = raw4_f(rb[2 * v]), r1 = raw4_f(rb[2 * v + 1]);
-      *(float2*)&Bs[buf][kp][c4 + (0 ^ sw)][0] = make_float2(r0.x, r1.x);
-      *(float2*)&Bs[buf][kp][c4 + (1 ^ sw)][0] = make_float2(r0.y, r1.y);
-      *(float2*)&Bs[buf][kp][c4 + (2 ^ sw)][0] = make_float2(r0.z, r1.z);
-      *(float2*)&Bs[buf][kp][c4 + (3 ^ sw)][0] = make_float2(r0.w, r1.w);
-      if constexpr (!AK) {
-        const float4 a0 = raw4_f(ra[2 * v]), a1 = raw4_f(ra[2 * v + 1]);
-        *(float2*)&As[buf][kp][c4 + (0 ^ sw)][0] = make_float2(a0.x, a1.x);
-        *(float2*)&As[buf][kp][c4 + (1 ^ sw)][0] = make_float2(a0.y, a1.y);
-        *(float2*)&As[buf][kp][c4 + (2 ^ sw)][0] = make_float2(a0.z, a1.z);
-        *(float2*)&As[buf][kp][c4 + (3 ^ sw)][0] = make_float2(a0.w, a1.w);
-      }
+      const int kp = idx >> 5, c4 = KL ? (4 * (idx & 31)) ^ ((kp >> 1) << 2) : 4 * (idx & 31), sw = KL ? 0 : (idx & 31) >> 3;
+      const float4 r0 = raw4_f(r[2 * v]), r1 = raw4_f(r[2 * v + 1]);
+      *(float2*)&s[kp][c4 + (0 ^ sw)][0] = make_float2(r0.x, r1.x);
+      *(float2*)&s[kp][c4 + (1 ^ sw)][0] = make_float2(r0.y, r1.y);
+      *(float2*)&s[kp][c4 + (2 ^ sw)][0] = make_float2(r0.z, r1.z);
+      *(float2*)&s[kp][c4 + (3 ^ sw)][0] = make_float2(r0.w, r1.w);
     }
-    if constexpr (AK) {
+  };
+  auto store_k = [&](float (*s)[128][2], const raw4_t (&r)[4], float f) {
 #pragma unroll
-      for (int v = 0; v < 4; ++v) {
-        const int idx = tid + GF_THREADS * v;
-        const int m = (idx >> 3) ^ ((idx & 7) << 2), kp = 2 * (idx & 7);
-        const float4 a = raw4_f(ra[v]);
-        *(float2*)&As[buf][kp][m][0] = make_float2(a.x, a.y);
-        *(float2*)&As[buf][kp + 1][m][0] = make_float2(a.z, a.w);
-      }
+    for (int v = 0; v < 4; ++v) {
+      const int idx = tid + GF_THREADS * v;
+      const int m = (idx >> 3) ^ ((idx & 7) << 2), kp = 2 * (idx & 7);
+      const float4 a = raw4_f(r[v]);
+      *(float2*)&s[kp][m][0] = make_float2(f * a.x, f * a.y);
+      *(float2*)&s[kp + 1][m][0] = make_float2(f * a.z, f * a.w);
     }
+  };
+  auto store = [&](int buf, int it) {
+    if (SEG && it >= nk0) {
+      store_m(Bs[buf], rb, std::integral_constant<bool, BK>{});
+      store_k(As[buf], ra, g.sign2);
+      return;
+    }
+    if constexpr (BK) store_k(Bs[buf], rb, 1.f);
+    else store_m(Bs[buf], rb, std::false_type{});
+    if constexpr (AK) store_k(As[buf], ra, 1.f);
+    else store_m(As[buf], ra, std::false_type{});
   };
 
 #pragma unroll
@@ -256,12 +284,12 @@ __global__ __launch_bounds__(GF_THREADS) void k_gemm_f32v(GemmF32Args g) {
 #pragma unroll
     for (int j = 0; j < 2; ++j) acc[i][j] = f32x16_t{};
 
-  load(ks0 * GV_BK);
-  store(0);
+  load(ks0);
+  store(0, ks0);
   __syncthreads();
   for (int it = ks0; it < ks1; ++it) {
     const int buf = (it - ks0) & 1;
-    if (it + 1 < ks1) load((it + 1) * GV_BK);
+    if (it + 1 < ks1) load(it + 1);
 #pragma unroll
     for (int kp = 0; kp < GV_BK / 2; ++kp) {
       float a[2], bb[2];
@@ -271,21 +299,26 @@ __global__ __launch_bounds__(GF_THREADS) void k_gemm_f32v(GemmF32Args g) {
         a[i] = As[buf][kp][wm * 64 + i * 32 + ((lane & 31) ^ sw)][lane >> 5];
       }
 #pragma unroll
-      for (int j = 0; j < 2; ++j) bb[j] = Bs[buf][kp][wn * 64 + j * 32 + ((lane & 31) ^ ((2 * wn + j) & 3))][lane >> 5];
+      for (int j = 0; j < 2; ++j) {
+        const int sw = BK ? (kp >> 1) << 2 : (2 * wn + j) & 3;
+        bb[j] = Bs[buf][kp][wn * 64 + j * 32 + ((lane & 31) ^ sw)][lane >> 5];
+      }
 #pragma unroll
       for (int i = 0; i < 2; ++i)
 #pragma unroll
         for (int j = 0; j < 2; ++j) acc[i][j] = mfma32x32x2f32(a[i], bb[j], acc[i][j]);
     }
     // the other buffer was last read in the previous stage, before the barrier
-    if (it + 1 < ks1) store(buf ^ 1);
+    if (it + 1 < ks1) store(buf ^ 1, it + 1);
     __syncthreads();
   }
   };
 
-  if (g.sk_part) {
-    sk_run(g, products, tid);
-    return;
+  if constexpr (!BK && !SEG) {
+    if (g.sk_part) {
+      sk_run(g, products, tid);
+      return;
+    }
   }
   int tbm, tbn, b;
   gv_tile(g, tbm, tbn, b);
@@ -528,18 +561,26 @@ __global__ __launch_bounds__(256) void k_gemm_sk_fix(GemmF32Args g) {
     if (nb + nn < g.N && mb + lane < g.M) C[(nb + nn) * g.sCm + (mb + lane) * g.sCn] = L[lane][nn];
 }
 
-// The aligned case of the pipelined kernel: returns 0 (A m-contiguous), 1
-// (A k-contiguous) or -1 (neither).
+// The aligned case of the pipelined kernel: bit 0: A k-contiguous (else
+// m-contiguous), bit 1: B k-contiguous (else n-contiguous); -1 for neither.
 int gemm_f32_vec_mode(const GemmF32Args& g) {
   auto al = [](const void* p) { return ((uintptr_t)p % 16) == 0; };
   auto m4 = [](int64_t v) { return v % 4 == 0; };
-  if (g.K <= 0 || !al(g.A) || !al(g.B)) return -1;
-  if (!(g.sBn == 1 && m4(g.sBk) && m4(g.N) && m4(g.sBb))) return -1;
   // buffer offsets are 31-bit byte offsets
   const int64_t lim = 0x7fffffffll - 16;
-  if (((int64_t)(g.K - 1) * g.sBk + g.N) * 4 > lim) return -1;
-  if (g.sAm == 1 && m4(g.sAk) && m4(g.M) && m4(g.sAb) && ((int64_t)(g.K - 1) * g.sAk + g.M) * 4 <= lim) return 0;
-  if (g.sAk == 1 && m4(g.sAm) && m4(g.K) && m4(g.sAb) && ((int64_t)(g.M - 1) * g.sAm + g.K) * 4 <= lim) return 1;
+  auto fits = [&](int64_t n, int64_t ld, int64_t c) { return ((n - 1) * ld + c) * 4 <= lim; };
+  if (g.K2 > 0) {
+    if (g.batch != 1 || g.sym_upper || g.split || !al(g.A2) || !al(g.B2) || !m4(g.sA2) || !m4(g.sB2) || !m4(g.K2) || !m4(g.N)) return -1;
+    if (!fits(g.V, g.sA2, g.K2) || !fits(g.K2, g.sB2, g.N)) return -1;
+    if (g.K == 0) return 1;  // the gathered rows alone
+  }
+  if (g.K <= 0 || !al(g.A) || !al(g.B) || !m4(g.sAb) || !m4(g.sBb)) return -1;
+  int mode;
+  if (g.sAm == 1 && g.K2 == 0 && m4(g.sAk) && m4(g.M) && fits(g.K, g.sAk, g.M)) mode = 0;
+  else if (g.sAk == 1 && m4(g.sAm) && m4(g.K) && fits(g.M, g.sAm, g.K)) mode = 1;
+  else return -1;
+  if (g.sBn == 1 && m4(g.sBk) && m4(g.N) && fits(g.K, g.sBk, g.N)) return mode;
+  if (mode == 1 && !g.split && !g.sym_upper && g.sBk == 1 && m4(g.sBn) && m4(g.K) && fits(g.N, g.sBn, g.K)) return 3;
   return -1;
 }
 
@@ -553,6 +594,7 @@ hipError_t launch_gemm_f32(const GemmF32Args& g, hipStream_t s) {
   if (g.split < 0 || g.split > GEMM_SPLIT_F16) return hipErrorInvalidValue;
   if ((g.pre_a || g.pre_b) && g.split != GEMM_SPLIT_F16) return hipErrorInvalidValue;
   if (g.sk_part && !g.sym_upper) return hipErrorInvalidValue;
+  if (g.K2 > 0 && (g.batch != 1 || g.split || g.sym_upper)) return hipErrorInvalidValue;
   const int ntm = (g.M + GV_BM - 1) / GV_BM;
   const dim3 vgrid = g.sk_part      ? dim3(gemm_f32_sk_plan(g.M, g.K, g.batch).nwg)
                      : g.sym_upper ? dim3(ntm * (ntm + 1) / 2, 1, g.batch)
@@ -568,10 +610,19 @@ hipError_t launch_gemm_f32(const GemmF32Args& g, hipStream_t s) {
   // stream-K fix-up, which sums up to K / 32 pieces per tile in turn, costs
   // more than the fp32 units' lower rate: [1024, 256] x 3: 26 -> 12 us.
   const int64_t tiles = (int64_t)ntm * ((g.N + GV_BN - 1) / GV_BN) * g.batch;
-  if (vm < 0 || (g.split ? g.sk_part && tiles < 48 : gemm_f32_small(g.M, g.N, g.batch))) {
+  // A k-contiguous B or gathered rows: the small kernel's time goes with the
+  // output's area, this one's with its rounds of 256 tiles.  They meet at
+  // about 132 whole tiles a round (this kernel's time over the small one's:
+  // K = 256, 112 tiles 1.15, 128: 1.06, 144: 1.02, 160: 0.90, 256: 0.66; with
+  // 64 gathered columns 112: 0.89; N = 64, K = 512, an area of 96: 1.12, 128: 0.96, 192:
+  // 1.02, 256: 0.89).
+  const bool few = vm == 3 || g.K2 > 0 ? (int64_t)g.M * g.N < 132ll * (GV_BM * GV_BN) * ((tiles + 255) / 256)
+                                       : gemm_f32_small(g.M, g.N, g.batch);
+  if (vm < 0 || (g.split ? g.sk_part && tiles < 48 : few)) {
     GemmF32sArgs q{};
-    q.nseg = 1;
-    q.seg[0] = {(const float*)g.A, g.sAm, g.sAk, (const float*)g.B, g.sBk, g.sBn, g.K, nullptr, 0, 0, 1.f};
+    if (g.K > 0 || g.K2 == 0)
+      q.seg[q.nseg++] = {(const float*)g.A, g.sAm, g.sAk, (const float*)g.B, g.sBk, g.sBn, g.K, nullptr, 0, 0, 1.f};
+    if (g.K2 > 0) q.seg[q.nseg++] = {g.A2, g.sA2, 1, g.B2, g.sB2, 1, g.K2, g.ids, 1, g.V, g.sign2};
     q.M = g.M; q.N = g.N; q.batch = g.batch; q.sAb = g.sAb; q.sBb = g.sBb;
     q.Cin = g.beta != 0.f ? g.Cin : nullptr; q.sCinm = g.sCinm; q.sCinn = g.sCinn; q.sCinb = g.sCinb;
     q.C = (float*)g.C; q.sCm = g.sCm; q.sCn = g.sCn; q.sCb = g.sCb;
@@ -598,8 +649,12 @@ hipError_t launch_gemm_f32(const GemmF32Args& g, hipStream_t s) {
     const hipError_t e = hipGetLastError();
     return e != hipSuccess ? e : sk_fix();
   }
-  if (vm) hipLaunchKernelGGL(k_gemm_f32v<true>, vgrid, dim3(GF_THREADS), 0, s, g);
-  else hipLaunchKernelGGL(k_gemm_f32v<false>, vgrid, dim3(GF_THREADS), 0, s, g);
+  const dim3 thr(GF_THREADS);
+  if (vm == 3 && g.K2 > 0) hipLaunchKernelGGL((k_gemm_f32v<true, true, true>), vgrid, thr, 0, s, g);
+  else if (vm == 3) hipLaunchKernelGGL((k_gemm_f32v<true, true, false>), vgrid, thr, 0, s, g);
+  else if (vm && g.K2 > 0) hipLaunchKernelGGL((k_gemm_f32v<true, false, true>), vgrid, thr, 0, s, g);
+  else if (vm) hipLaunchKernelGGL((k_gemm_f32v<true, false, false>), vgrid, thr, 0, s, g);
+  else hipLaunchKernelGGL((k_gemm_f32v<false, false, false>), vgrid, thr, 0, s, g);
   const hipError_t e = hipGetLastError();
   return e != hipSuccess ? e : sk_fix();
 }

@@ -31,7 +31,10 @@ bool gemm_tn_gathers(const TnArgs& g);
 hipError_t launch_gemm_tn_deep(const TnArgs& g, hipStream_t s);  // its kernel for few tiles
 
 // ---------------------------------------------------------------- fp32 GEMM
-// C[b](m,n) = alpha sum_k A[b](m,k) B[b](k,n) + beta Cin[b](m,n), all fp32; Cin may be null.
+// C[b](m,n) = alpha (sum_k A[b](m,k) B[b](k,n)
+//             + sign2 sum_{i < K2} A2[ids[m] sA2 + i] B2[i sB2 + n]) + beta Cin[b](m,n),
+// all fp32; Cin may be null, K2 0 (else batch 1, no split, not symmetric; ids
+// outside [0, V) read row 0).
 enum { GEMM_SPLIT_NONE = 0, GEMM_SPLIT_F16 = 1 };
 struct GemmF32Args {
   const void* A; int64_t sAm, sAk, sAb;
@@ -40,6 +43,7 @@ struct GemmF32Args {
   void* C; int64_t sCm, sCn, sCb;
   int M, N, K, batch;
   float alpha, beta;
+  const float* A2; int64_t sA2; const float* B2; int64_t sB2; const int32_t* ids; int K2, V; float sign2;
   int split;  // aligned operands: GEMM_SPLIT_F16 takes the products as
              // hi.hi + hi.lo + lo.hi of fp16 pieces of 2^8 x (|operands| < 255)
   const float* pre_a; const float* pre_b;  // GEMM_SPLIT_F16 only: per-batch factors of A and B

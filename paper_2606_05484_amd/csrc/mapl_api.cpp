@@ -346,6 +346,22 @@ GemmF32Args gemm(int M, int N, int K) {
   return g;
 }
 
+// The anchor term of Eqs. 1-2 in the same product: + sign A[ids] B, A [V, k], B [k, ldb].
+void add_anchor(GemmF32Args& g, const void* A, int64_t k, const int32_t* ids, int64_t V, const void* B, int64_t ldb,
+                float sign = 1.f) {
+  g.A2 = (const float*)A; g.sA2 = k; g.K2 = (int)k; g.ids = ids; g.V = (int)V;
+  g.B2 = (const float*)B; g.sB2 = ldb; g.sign2 = sign;
+}
+// out = Z + A[ids] B, Z and out [T, r], B [k, r].
+GemmF32Args anchored(int64_t T, int64_t r, const float* Z, const void* A, int64_t k, const int32_t* ids, int64_t V,
+                     const void* B, float* out) {
+  GemmF32Args g = gemm((int)T, (int)r, 0);
+  g.Cin = Z; g.sCinm = r; g.sCinn = 1; g.beta = 1.f;
+  g.C = out; g.sCm = r; g.sCn = 1;
+  add_anchor(g, A, k, ids, V, B, r);
+  return g;
+}
+
 // The latency-bound fp32 product's builders: an M x N output of row stride ldc
 // and its segments (see GemmF32Seg).
 GemmF32sArgs gemm_s(int64_t M, int64_t N, void* C, int64_t ldc) {
@@ -513,21 +529,14 @@ extern "C" int mapl_encode(const mapl_codec_desc* desc, const void* X, const int
     LAUNCH("enc:gemm_f32", launch_gemm_f32(g, s));
     Bk = BU;
   }
-  // X U and -A_s[ids] Bk in one launch where the output is small, else the
-  // second added to the first
-  GemmF32sArgs q = gemm_s(T, r, out, r);
-  if (gemm_f32_small(T, r, 1)) {
-    add_seg(q, X, d, 1, U, r, 1, d);
-  } else {
+  {
     GemmF32Args g = gemm((int)T, (int)r, (int)d);
     g.A = X; g.sAm = d; g.sAk = 1;
     g.B = U; g.sBk = r; g.sBn = 1;
     g.C = out; g.sCm = r; g.sCn = 1;
+    if (k > 0) add_anchor(g, A_s, k, ids, D.V, Bk, r, -1.f);
     LAUNCH("enc:gemm_f32", launch_gemm_f32(g, s));
-    add_cin(q, out, r);
   }
-  if (k > 0) add_seg(q, A_s, k, 1, Bk, r, 1, k, -1.f, ids, 1, D.V);
-  if (q.nseg > 0) LAUNCH("enc:gemm_f32s", launch_gemm_f32s(q, s));
   if (grouped(D))
     LAUNCH("enc:grvq", launch_grvq(out, C, (int)T, (int)r, D.L, D.K, (uint8_t*)payload, s));
   else if (D.L > 0)
@@ -611,17 +620,16 @@ extern "C" int mapl_decode(const mapl_codec_desc* desc, const void* payload, con
   }
   if (!amb && k > 0) {
     float* z2 = at<float>(ws, Lo.z2);
-    GemmF32sArgs g = gemm_s(T, r, z2, r);
-    add_cin(g, Zh, r);
-    add_seg(g, A_r, k, 1, B_r, r, 1, k, 1.f, ids, 1, D.V);
-    LAUNCH("dec:gemm_f32s", launch_gemm_f32s(g, s));
+    LAUNCH("dec:gemm_f32", launch_gemm_f32(anchored(T, r, Zh, A_r, k, ids, D.V, B_r, z2), s));
     Zh = z2;
   }
   {
-    GemmF32sArgs g = gemm_s(T, d, Xhat, d);
-    add_seg(g, Zh, r, 1, U, 1, r, r);
-    if (amb && k > 0) add_seg(g, A_r, k, 1, B_r, d, 1, k, 1.f, ids, 1, D.V);
-    LAUNCH("dec:gemm_f32s", launch_gemm_f32s(g, s));
+    GemmF32Args g = gemm((int)T, (int)d, (int)r);
+    g.A = Zh; g.sAm = r; g.sAk = 1;
+    g.B = U; g.sBk = 1; g.sBn = r;
+    g.C = Xhat; g.sCm = d; g.sCn = 1;
+    if (amb && k > 0) add_anchor(g, A_r, k, ids, D.V, B_r, d);
+    LAUNCH("dec:gemm_f32", launch_gemm_f32(g, s));
   }
   return MAPL_OK;
 }
@@ -752,10 +760,7 @@ int decode_bwd_impl(const mapl_codec_desc* desc, const void* dXhat, const void* 
   }
   if (need_anchor) {
     float* z2 = at<float>(ws, Lo.z2);
-    GemmF32sArgs g = gemm_s(T, r, z2, r);
-    add_cin(g, Zh, r);
-    add_seg(g, A_r, k, 1, B_r, r, 1, k, 1.f, ids, 1, D.V);
-    LAUNCH("dec_bwd:gemm_f32s", launch_gemm_f32s(g, s));
+    LAUNCH("dec_bwd:gemm_f32", launch_gemm_f32(anchored(T, r, Zh, A_r, k, ids, D.V, B_r, z2), s));
     Zh = z2;
   }
   {
@@ -930,21 +935,31 @@ extern "C" int mapl_encode_bwd(const mapl_codec_desc* desc, const void* dZ, cons
     add_seg(g, A_s, 1, k, dZ, r, 1, T, 1.f, ids, 2, D.V);
     LAUNCH("enc_bwd:gemm_f32s", launch_gemm_f32s(g, s));
   }
-  GemmF32sArgs q = gemm_s(d, r, dU, r);
-  if (gemm_f32_small(d, r, 1)) {
-    add_seg(q, X, 1, d, dZ, r, 1, T);
-    if (accumulate_dU) add_cin(q, dU, r);
-  } else {
+  if (need_anchor && gemm_f32_small(d, r, 1)) {
+    GemmF32sArgs g = gemm_s(d, r, dU, r);
+    add_seg(g, X, 1, d, dZ, r, 1, T);
+    add_seg(g, B_s, 1, d, Wm, r, 1, k, -1.f);
+    if (accumulate_dU) add_cin(g, dU, r);
+    LAUNCH("enc_bwd:gemm_f32s", launch_gemm_f32s(g, s));
+    return MAPL_OK;
+  }
+  {
     GemmF32Args g = gemm((int)d, (int)r, (int)T);
     g.A = X; g.sAm = 1; g.sAk = d;
     g.B = dZ; g.sBk = r; g.sBn = 1;
     if (accumulate_dU) { g.Cin = dU; g.sCinm = r; g.sCinn = 1; g.beta = 1.f; }
     g.C = dU; g.sCm = r; g.sCn = 1;
     LAUNCH("enc_bwd:gemm_f32", launch_gemm_f32(g, s));
-    add_cin(q, dU, r);
   }
-  if (need_anchor) add_seg(q, B_s, 1, d, Wm, r, 1, k, -1.f);
-  if (q.nseg > 0) LAUNCH("enc_bwd:gemm_f32s", launch_gemm_f32s(q, s));
+  if (need_anchor) {
+    GemmF32Args g = gemm((int)d, (int)r, (int)k);
+    g.A = B_s; g.sAm = 1; g.sAk = d;
+    g.B = Wm; g.sBk = r; g.sBn = 1;
+    g.Cin = dU; g.sCinm = r; g.sCinn = 1; g.beta = 1.f;
+    g.C = dU; g.sCm = r; g.sCn = 1;
+    g.alpha = -1.f;
+    LAUNCH("enc_bwd:gemm_f32", launch_gemm_f32(g, s));
+  }
   return MAPL_OK;
 }
 

@@ -15,10 +15,13 @@ pytestmark = pytest.mark.gpu
 
 @pytest.mark.parametrize("space", ["ambient", "coord"])
 @pytest.mark.parametrize("T,d,r,k", [(1, 64, 32, 16), (31, 64, 64, 48), (33, 320, 96, 64), (257, 192, 32, 0),
-                                     (1025, 576, 160, 112), (15400, 128, 128, 16), (300, 7808, 160, 32)])
+                                     (1025, 576, 160, 112), (15400, 128, 128, 16), (300, 7808, 160, 32),
+                                     (4500, 512, 96, 48), (18001, 128, 128, 16), (26001, 192, 160, 112)])
 def test_fp32_chain(T, d, r, k, space):
-    """(15400, r = 128) has 121 128-row tiles: the projection takes the large
-    kernel and adds the anchor term to it; (d = 7808, r = 160): dU likewise."""
+    """(d = 7808, r = 160): dU takes the large kernel and the anchor term is
+    added to it.  The last three: the large kernel with a k-contiguous B and
+    gathered rows (lift, dX), the second also with gathered rows alone (the
+    coordinate anchor of 18001 x 128) and in the projection."""
     print("fp32", T, d, r, k, space, flush=True)
     x = synth.codec_inputs(None, seed=41, T=T, d=d, r=r, V=200, k=k, L=0, K=0, dtype="f32", alpha=0.8, n_out=4,
                            cb_sigma=None, gscale=1.0, anchor_space=space, rotate=d <= 1024)
