@@ -3,7 +3,7 @@
 // table row of its id; the rows are summed per id in a fixed order, so the
 // result is reproducible bit for bit (no floating-point atomics):
 //   1. the (id, token) pairs ordered so that equal ids are adjacent and keep
-//      their token order.  Up to 32768 tokens: a bin per 256 ids, one
+//      their token order.  Up to 32768 tokens (anchor_sort_fits): a bin per 256 ids, one
 //      workgroup per bin, beside the call's other preparation
 //      (k_anchor_prep); longer lists by a stable LSD radix sort, 8-bit digits
 //      (per-tile digit histograms, one exclusive scan, a stable scatter).
@@ -83,7 +83,15 @@ __device__ __forceinline__ void sort_bin(const AnchorPrepArgs& a, int b, uint32_
   }
   __syncthreads();
   const int per = (m + AP_THREADS - 1) / AP_THREADS * 64, i0 = wave * per, i1 = min(m, i0 + per);
-  for (int i = i0 + lane; i < i1; i += 64) atomicAdd(&cnt[wave][list[i] >> 24], 1u);
+  // lanes of lane 0's digit as one addition: additions to one word are done
+  // one by one (nine tokens in ten of one id: T = 32768, V = 32000: the
+  // call 96.5 us that way, 77.2 so)
+  for (int i = i0 + lane; i < i1; i += 64) {
+    const uint32_t dg = list[i] >> 24, d0 = __builtin_amdgcn_readfirstlane(dg);
+    const uint64_t same = __ballot(dg == d0);
+    if (lane == 0) atomicAdd(&cnt[wave][d0], (uint32_t)__popcll(same));
+    else if (dg != d0) atomicAdd(&cnt[wave][dg], 1u);
+  }
   __syncthreads();
   // exclusive offsets, digit-major: thread d < 256 its digit's total, a scan
   // over the digits by wave shuffles, then the waves in order
@@ -480,8 +488,12 @@ void launch_segsum_nc(const AnchorSegArgs& a, hipStream_t s) {
 }  // namespace
 
 // A list of 32768 tokens fits the LDS beside the counts; 512 bins (V up to
-// 131072) read the ids 512 times, 64 MB from the L2s at most.
-bool anchor_sort_fits(int64_t n, int64_t V) { return n <= 32 * AP_THREADS && V <= 131072; }
+// 131072) read the ids 512 times, 64 MB from the L2s at most.  A single bin
+// (V <= 256) scatters every pair from one CU, where the radix sort needs one
+// pass: the call (k = 32) with the bin / the radix sort, us: T = 8192: 27.5 /
+// 32.7, 12000: 34.9 / 33.5, 16384: 38.5 / 34.2, 32768: 61.8 / 40.7; with two
+// bins (V = 512) 32768: 45.9 / 57.4.
+bool anchor_sort_fits(int64_t n, int64_t V) { return n <= (V <= 256 ? 10 : 32) * AP_THREADS && V <= 131072; }
 
 hipError_t launch_anchor_prep(const AnchorPrepArgs& a, hipStream_t s) {
   AnchorPrepArgs g = a;

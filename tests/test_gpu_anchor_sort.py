@@ -1,6 +1,6 @@
 """The binned sort of the anchor-table gradient at its edges: token
 counts around each instance and beyond the largest (the multi-launch sort),
-one id for every token, ids at both ends of the table, tables of one bin
+one id for every token or for most, ids at both ends of the table, tables of one bin
 and beyond the most, and companions with padded rows.  dY rows are small
 integers and B is a scaled identity block, so every sum is exact and the
 comparison is equality."""
@@ -16,7 +16,8 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("T,V,k,ids", [
     (1, 300, 16, "zipf"), (63, 300, 48, "rand"), (2048, 5, 64, "rand"), (2049, 32000, 64, "zipf"), (8192, 256, 80, "one"),
     (8193, 65534, 64, "ends"), (16385, 40000, 128, "rand"), (32767, 65534, 16, "zipf"), (32768, 1000, 144, "one"),
-    (32769, 1000, 64, "zipf"), (3000, 131072, 32, "ends"), (5000, 131073, 64, "rand")])
+    (32769, 1000, 64, "zipf"), (3000, 131072, 32, "ends"), (5000, 131073, 64, "rand"), (10240, 256, 16, "rand"),
+    (10241, 256, 48, "zipf"), (30001, 40000, 32, "most")])
 @pytest.mark.parametrize("accumulate", [0, 1])
 def test_receiver_table_exact(T, V, k, ids, accumulate):
     print("anchor sort", T, V, k, ids, accumulate, flush=True)
@@ -27,6 +28,8 @@ def test_receiver_table_exact(T, V, k, ids, accumulate):
         tid = rng.choice(V, T, p=p / p.sum())
     elif ids == "one":
         tid = np.full(T, V - 1)
+    elif ids == "most":
+        tid = np.where(rng.uniform(size=T) < 0.9, 5, rng.integers(0, V, T))
     elif ids == "ends":
         tid = rng.choice([0, 1, V - 2, V - 1], T)
     else:
