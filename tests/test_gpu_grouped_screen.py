@@ -35,7 +35,7 @@ def exact_codes(Z, C):
 
 
 @pytest.mark.parametrize("T,r,L,K", [(1, 64, 1, 32), (31, 64, 2, 64), (33, 128, 1, 96), (127, 64, 8, 128),
-                                     (129, 96, 3, 160), (300, 64, 2, 256), (257, 32, 1, 224)])
+                                     (129, 96, 3, 160), (300, 64, 2, 256), (257, 32, 1, 224), (257, 64, 3, 32)])
 @pytest.mark.parametrize("kind", ["ties", "spread", "far"])
 def test_codes_are_the_first_nearest(T, r, L, K, kind):
     """ties: small integer coordinates, so most searches have several
