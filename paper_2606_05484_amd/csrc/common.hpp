@@ -69,57 +69,6 @@ __device__ __forceinline__ uint32_t pack_h2(float lo, float hi) {
 }
 __device__ __forceinline__ float h2f(uint32_t b) { return (float)__builtin_bit_cast(_Float16, (uint16_t)b); }
 
-// Screening margin of the RVQ kernel for residual width R.  Everything is in
-// the round's scaled units: codewords and residuals times a power of two
-// that puts the codebook's larger coordinates near 2^5 (see
-// prep_codebook_block).  With R~ = fp16(R), C~_j = fp16(C_j) (saturated),
-// eR = ||R - R~|| + RVQ_FLUSH and e_j = ||C_j - C~_j|| + RVQ_FLUSH (2^-14
-// per coordinate: as much as a matrix unit that took subnormal inputs as
-// zero could add), the screen's score s~_j = ||C_j||^2 - 2 R~.C~_j (the
-// squared norm exact after the first k-step: three bf16 pieces that sum to
-// it exactly, times ones) satisfies
-//   |s~_j - s_j| <= 2 ||R|| e_j + 2 eR (1 + 2^-8) ||C_j||
-//                   + ka ||R|| ||C_j|| + k2 ||C_j||^2  =: Delta_j, where
-// 2 R.C_j - 2 R~.C~_j = 2 R.(C_j - C~_j) + 2 (R - R~).C~_j gives the first
-// two terms (Cauchy-Schwarz; ||C~_j|| <= (1 + 2^-11) ||C_j|| + 2^-25 sqrt(R),
-// saturation only shrinks it), and
-//   ka = (8 R 2^-24            (fp32 accumulation of 2R~.C~, any order,
-//                               relative error up to 2 u per addition)
-//        + 2^-20 + 2^-16) (1 + 2^-7)  (norm rounding; an index tag in the
-//                               low 4 mantissa bits, which moves a score by
-//                               less than 2^-19 of |s~_j| <= ||C_j||^2 +
-//                               2.02 ||R|| ||C_j||, doubled; ||R~|| ||C~||
-//                               against ||R|| ||C||)
-//   k2 = 4 (R + 4) 2^-24 + 2^-17 (accumulation and fp32 rounding of
-//                               ||C_j||^2; the index tag, doubled)
-// fp16 pieces (11 significant bits) keep the margin at about 2^-10
-// ||R|| ||C_j||, a seventh of what bf16 pieces leave: on data-drawn
-// codebooks a third of the token-rounds was undecided with bf16 (1B-model
-// boundary, K = 1024) and one in twenty is with fp16.
-__host__ __device__ constexpr float rvq_margin_ka(int R) {
-  return (8.0f * R / 16777216.0f + 1.0f / 1048576.0f + 1.0f / 65536.0f) * 1.0078125f;
-}
-__host__ __device__ constexpr float rvq_margin_k2(int R) { return 4.0f * (R + 4) / 16777216.0f + 1.0f / 131072.0f; }
-__host__ __device__ constexpr float rvq_flush(int R) {  // 2^-14 sqrt(R), rounded up
-  return (R <= 64 ? 8.0f : R <= 128 ? 11.32f : 16.0f) / 16384.0f;
-}
-
-// The screen of the RVQ kernel computes, per codeword, a certified lower bound
-// of the exact score s_j = ||C_j||^2 - 2 R . C_j rather than the score itself:
-// the norm columns of a codeword row hold (1 - RVQ_K2_SLACK k2) ||C_j||^2
-// (three bf16 pieces, exact), ||C_j|| rounded up (two bf16 pieces) and e_j
-// rounded up (one piece); the token's operand multiplies them by ones, by -b
-// with b = (2 eR (1 + 2^-7) + ka ||R||) RVQ_K1_SLACK and by -c with
-// c = 2 ||R|| RVQ_K1_SLACK, each rounded up to bf16, so that the accumulator
-// ends at
-//   L_j = s~_j - k2' ||C_j||^2 - b ||C_j||' - c e_j'  <=  s_j.
-// The subtracted amount is at most RVQ_SUB_FACTOR Delta_j (bf16 rounding up
-// of the coefficients and of e_j, 2^-7 each, and the slack), so
-// s_j <= L_j + (RVQ_SUB_FACTOR + 1) Delta_j.
-constexpr float RVQ_K1_SLACK = 1.0002f * 1.01f;
-constexpr float RVQ_K2_SLACK = 1.01f;
-constexpr float RVQ_SUB_FACTOR = 1.03f;
-
 // bf16 bit pattern of a non-negative finite float, rounded toward +infinity.
 __device__ __forceinline__ uint32_t bf16_up(float f) {
   const uint32_t b = __float_as_uint(f);

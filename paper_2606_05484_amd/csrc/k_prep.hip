@@ -9,6 +9,7 @@
 //                   receiver's anchor row (Eq. 2)
 #include "common.hpp"
 #include "kernels.hpp"
+#include "rvq_margin.hpp"
 
 namespace mapl {
 
@@ -60,8 +61,7 @@ __device__ __forceinline__ void transpose_tile(int bx, int by, const void* __res
 
 // The power of two that takes a round's codebook into the screen's units:
 // the largest of a sample of its coordinates (four columns, other ones for
-// each codeword, of up to 256 codewords) lands in [2^5, 2^6).  fp16 then
-// keeps 11 bits of every coordinate from 2^-19 of that up to 2^10 times it.
+// each codeword, of up to 256 codewords) lands in [2^RVQ_CB_EXP, twice that).
 // Every block computes the same value from the same sample (4 KB, read
 // while the block's rows are on their way); a poor sample costs speed only,
 // because the margins use the rounding errors that really occurred.
@@ -70,7 +70,8 @@ __device__ __forceinline__ float rvq_round_scale(const float* __restrict__ C, in
   const int64_t stride = K / n;
   float m = 0.f;
   for (int i = threadIdx.x; i < n; i += 256) {
-    const float4 v = *(const float4*)(C + (int64_t)i * stride * r + 4 * ((i * 17) % q4));
+    const int64_t j = i * stride + (i * 5) % stride;  // no regular rows: every second codeword may be unlike the others
+    const float4 v = *(const float4*)(C + j * r + 4 * ((i * 17) % q4));
     m = fmaxf(m, fmaxf(fmaxf(fabsf(v.x), fabsf(v.y)), fmaxf(fabsf(v.z), fabsf(v.w))));
   }
 #pragma unroll
@@ -79,11 +80,11 @@ __device__ __forceinline__ float rvq_round_scale(const float* __restrict__ C, in
   __syncthreads();
   m = fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3]));
   if (!(m > 0.f)) return 1.f;
-  // exponent field e of m: 2^(5 - (e - 127)), kept a normal number, and so
-  // that the rounds' -2 times it is finite too (an infinite factor would make
-  // NaN of a residual coordinate that is exactly zero)
+  // exponent field e of m: 2^(RVQ_CB_EXP - (e - 127)), kept a normal number,
+  // and so that the rounds' -2 times it is finite too (an infinite factor
+  // would make NaN of a residual coordinate that is exactly zero)
   const int e = (int)(__float_as_uint(m) >> 23);
-  return __uint_as_float((uint32_t)min(max(127 + 5 + 127 - e, 1), 253) << 23);
+  return __uint_as_float((uint32_t)min(max(127 + RVQ_CB_EXP + 127 - e, 1), 253) << 23);
 }
 
 // One wave per (stage, codeword slot of a 64-codeword chunk): the fp16 copy
@@ -128,7 +129,7 @@ __device__ __forceinline__ void prep_codebook_block(int bx, const float* __restr
   s = wave_sum(s);
   es = wave_sum(es);
   // ||C_j - fp16(C_j)|| rounded up: es carries at most r ulps of accumulation error
-  const float eu = sqrtf(es) * (1.0f + 1.0f / 32768.0f) + rvq_flush(r);
+  const float eu = sqrtf(es) * (1.0f + 1.0f / 32768.0f) + RVQ_TINY;
   if (j < K && lane < 16) {
     // columns r .. r+2: the reduced norm n' = s - 1.01 k2 s in three pieces
     // (each difference exact in fp32, so they sum to n' exactly); columns

@@ -53,6 +53,7 @@
 // Each lane thus sees the scores of ONE token for 16 codewords per tile;
 // the fold of one tile into its two smallest keys overlaps the matrix products of the
 // next.  The two lane halves that share a token merge at the end of a pass.
+#include "rvq_margin.hpp"
 #include "tn_gemm.hpp"
 
 namespace mapl {
@@ -197,14 +198,16 @@ __device__ __forceinline__ void rvq_rounds(const RvqArgs& a, bf16_t* s0, bf16_t*
     auto issue = [&](int q, bf16_t* sc) { issue_l(l, q, sc); };
 
     // In the round's scaled units (the residual times the codebook's power
-    // of two): fp16(-2 R_l) in B-fragment layout, ||R_l||^2 and the rounding
+    // of two and tsc): fp16(-2 R_l) in B-fragment layout, ||R_l||^2 and the rounding
     // error ||R_l - R~_l||^2 with -2 R~ = fp16(-2 R) (the difference is exact
     // in fp32).  Coordinates stay scaled in this block only: res keeps the
     // fp32 residual.
     const float m2s = -2.f * __uint_as_float((uint32_t)__builtin_amdgcn_readlane(__float_as_int(scales), l));
+    float tsc = RVQ_TOK_SCALE;
     uint4 rb[NK16];
     float rn2, er2;
-    auto operand = [&](float f) {
+    auto operand = [&]() {
+      const float f = m2s * tsc;
       rn2 = er2 = 0.f;
 #pragma unroll
       for (int s = 0; s < NK16; ++s) {
@@ -225,33 +228,33 @@ __device__ __forceinline__ void rvq_rounds(const RvqArgs& a, bf16_t* s0, bf16_t*
       rn2 += __shfl_xor(rn2, 32, WAVE);
       er2 += __shfl_xor(er2, 32, WAVE);
     };
-    operand(m2s);
-    // A coordinate past fp16's range makes er2 infinite.  Such a token's whole
-    // operand, norm step included, takes a power of two tsc of its own: its
-    // scores and their bounds are all tsc times what they were, so its
-    // decisions are the same.  (Without it every such token was scored
-    // against the whole codebook: T = 8192, K = 1024, codewords 2^-12 of the
-    // residuals: 10.9 ms.)  Up to 2^49 only; larger ones are `hard`, see
-    // below.
-    float tsc = 1.f;
-    if (__any(!(er2 < INFINITY))) {
+    operand();
+    // A coordinate past fp16's range makes er2 infinite, and a residual far
+    // below the codebook's scale loses bits.  Such a token's whole operand,
+    // norm step included, takes a power of two tsc of its own: its scores and
+    // their bounds are all multiplied by it, so its decisions are the same.
+    // (Otherwise it is scored against the whole codebook: T = 8192, K =
+    // 1024, codewords 2^-12 of the residuals: 10.9 ms.)  From 2^-60 to 2^49
+    // only; larger ones are `hard`, see below.
+    if (__any(!(er2 < INFINITY) | ((rn2 < R * 0x1p-20f) & (rn2 > 0.f)))) {
       float mx = 0.f;
 #pragma unroll
       for (int s = 0; s < NK16; ++s)
 #pragma unroll
         for (int e = 0; e < 8; ++e) mx = fmaxf(mx, fabsf(res[s][e]));
       mx = fmaxf(mx, __shfl_xor(mx, 32, WAVE)) * fabsf(m2s);
+      const bool far = mx * RVQ_TOK_SCALE >= 65504.f || mx < 0x1p-3f;
       // 2^14 <= tsc mx < 2^15
-      if (mx >= 65504.f && mx < 0x1p49f) tsc = __uint_as_float((127u + 14u + 127u - (__float_as_uint(mx) >> 23)) << 23);
-      operand(m2s * tsc);
+      if (far && mx >= 0x1p-60f && mx < 0x1p49f) tsc = __uint_as_float((127u + 14u + 127u - (__float_as_uint(mx) >> 23)) << 23);
+      operand();
     }
     // norms of R, half those of -2 R, rounded up (each sum carries at most R
     // ulps of accumulation error)
-    const float rnorm = 0.5f * sqrtf(rn2) * (1.0f + 1.0f / 32768.0f);
-    const float enorm = 0.5f * sqrtf(er2) * (1.0f + 1.0f / 32768.0f) + rvq_flush(R);
+    const float rnorm = 0.5f * sqrtf(rn2) * (1.0f + 1.0f / 32768.0f) + RVQ_TINY;
+    const float enorm = 0.5f * sqrtf(er2) * (1.0f + 1.0f / 32768.0f) + RVQ_TINY;
     // the margin's coefficient of ||C_j|| (b) and of e_j (c)
     const float bco = 2.0f * enorm * 1.0078125f + rvq_margin_ka(R) * rnorm;
-    const float cco = 2.0f * rnorm;
+    const float cco = 2.0f * (rnorm + enorm);
 
     // One screening pass over all chunks.  Per 32-codeword tile the fold
     // callbacks see begin(), score(acc, tile, e) for e = 0..15, end(tile).
@@ -428,7 +431,7 @@ __device__ __forceinline__ void rvq_rounds(const RvqArgs& a, bf16_t* s0, bf16_t*
       // bounds are not finite): every codeword is a candidate.  A NaN residual
       // has no nearest codeword and takes 0.
       const bool nan = rn2 != rn2;
-      const bool hard = !(rn2 < 1e30f) || !(fabsf(thr) < 1e37f * tsc);
+      const bool hard = !(rn2 < 1e30f) || !(fabsf(thr) < 1e37f * fminf(tsc, 1.f));
       open = valid && !nan && (hard || !(k2 > thr));
       j1 = nan ? 0 : j1;
       // a token whose third keys exceed U is rescored from its listed first

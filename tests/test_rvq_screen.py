@@ -3,10 +3,14 @@ candidate lists.
 
 The screen runs in units of a power of two per round (from a sample of the
 codebook's coordinates) and decides a token only where its certified bounds
-do; every code is still the exact fp32 argmin.  Checked here: the bound
-itself in float64 (CPU), and on the GPU codebooks of extreme scale, codewords
+do; every code is still the exact fp32 argmin.  Checked here: the bounds
+themselves, in the kernels' arithmetic and with their constants (CPU), and on the GPU codebooks of extreme scale, codewords
 and tokens far outside fp16's range, and near ties that fall on the two
 lane halves and their first, second and third keys."""
+import os
+import shutil
+import subprocess
+
 import numpy as np
 import pytest
 
@@ -17,35 +21,124 @@ from _helpers import Dev, codes_np, compare_codes, descr, f64, run_encode, stres
 SMALL = dict(T=300, d=512, r=64, V=300, k=16, L=2, K=64, dtype="bf16", alpha=0.8, n_out=4, cb_sigma=None, gscale=1.0)
 
 
-def _flush16(x):
-    """fp16 rounding, saturated, subnormals taken as zero (the worst a matrix unit may do)."""
-    y = np.clip(x, -65504.0, 65504.0).astype(np.float16).astype(np.float64)
-    return np.where(np.abs(y) < 2.0 ** -14, 0.0, y)
+CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2606_05484_amd", "csrc")
+PROG = r"""
+#include <cstdio>
+#include <initializer_list>
+#include "rvq_margin.hpp"
+int main() {
+  using namespace mapl;
+  for (int R : {64, 128, 256}) std::printf("%d %.9g %.9g\n", R, rvq_margin_ka(R), rvq_margin_k2(R));
+  std::printf("0 %.9g %.9g %.9g %.9g %d %.9g\n", RVQ_K1_SLACK, RVQ_K2_SLACK, RVQ_SUB_FACTOR, RVQ_TINY, RVQ_CB_EXP,
+              RVQ_TOK_SCALE);
+  return 0;
+}
+"""
+
+
+@pytest.fixture(scope="module")
+def bounds(tmp_path_factory):
+    """The kernels' constants, from their header."""
+    cxx = shutil.which("g++") or shutil.which("c++")
+    if cxx is None:
+        pytest.skip("no host C++ compiler")
+    d = tmp_path_factory.mktemp("rvq_margin")
+    (d / "m.cpp").write_text(PROG)
+    subprocess.run([cxx, "-std=c++17", "-I", CSRC, str(d / "m.cpp"), "-o", str(d / "m")], check=True)
+    rows = [l.split() for l in subprocess.run([str(d / "m")], check=True, capture_output=True, text=True).stdout.splitlines()]
+    out = {int(r[0]): (float(r[1]), float(r[2])) for r in rows[:3]}
+    return out, [float(v) for v in rows[3][1:]]
+
+
+f32 = np.float32
+
+
+def _bf(v):
+    b = np.asarray(v, f32).view(np.uint32).astype(np.uint64)
+    return (((b + 0x7FFF + ((b >> 16) & 1)) >> 16) << 16).astype(np.uint32).view(f32)
+
+
+def _bf_up(v):  # of non-negative values
+    b = np.asarray(v, f32).view(np.uint32)
+    return (((b >> 16) + ((b & 0xFFFF) != 0)) << 16).astype(np.uint32).view(f32)
+
+
+def _bf_trunc(v):
+    return (np.asarray(v, f32).view(np.uint32) & np.uint32(0xFFFF0000)).view(f32)
+
+
+def _f16(v):
+    with np.errstate(over="ignore"):
+        return v.astype(np.float16).astype(f32)
 
 
 @pytest.mark.parametrize("r", [64, 128, 256])
-@pytest.mark.parametrize("spread", [0.0, 3.0, 30.0])
-def test_margin_bounds_the_screen_error(r, spread):
-    """|s~_j - s_j| <= Delta_j with the kernel's formula, the kernel's error
-    norms taken with subnormals kept and the per-coordinate allowance added."""
-    rng = np.random.default_rng(r + int(spread))
-    mag = np.exp(-spread * rng.uniform(0, 1, (2, r)))  # coordinates over e^30 of magnitudes
-    R = 2.0 ** rng.uniform(-4, 9, (200, 1)) * mag[0] * rng.standard_normal((200, r))
-    C = 40.0 * mag[1] * rng.standard_normal((100, r))
-    C[0] *= 1e4  # saturates
+@pytest.mark.parametrize("grid", [False, True])
+@pytest.mark.parametrize("spread,size", [(0.0, 0), (3.0, 0), (30.0, 0), (0.0, -18), (0.0, 14), (0.0, -30), (3.0, 30)])
+def test_margin_bounds_the_screen(bounds, r, spread, size, grid):
+    """L_j <= s_j <= L_j + (RVQ_SUB_FACTOR + 1) Delta_j for the screen's score
+    L_j as the kernels form it (fp16 coordinates, reduced norm and bound
+    columns in bf16 pieces, fp32 sums in any order, a 4-bit tag), with the
+    bounds from its own rounding errors and the header's constants; tokens
+    within and 2^size outside the codebook's scale, coordinates over e^spread
+    of magnitudes, codewords saturated, subnormal and zero.  grid: coordinates
+    that fp16 holds exactly, so that only ka and k2 (sums, norms, tag) are
+    left in the bounds; one token is its codeword, one opposite to it."""
+    per_r, (k1s, k2s, sub, tiny, cbexp, tok) = bounds
+    ka, k2 = per_r[r]
+    rng = np.random.default_rng(r + int(spread) + 100 * (size + 40))
+    NT, NC = 24, 40
+    mag = np.exp(-spread * rng.uniform(0, 1, (2, r)))
+    C = 2.0 ** (cbexp - 1) * mag[1] * rng.standard_normal((NC, r))
+    C[0] *= 1e4   # saturates
     C[1] = 0.0
-    Rq, Cq = _flush16(-2 * R) / -2, _flush16(C)
-    ka = (8 * r / 2 ** 24 + 2.0 ** -20 + 2.0 ** -16) * 1.0078125
-    k2 = 4 * (r + 4) / 2 ** 24 + 2.0 ** -17
-    flush = 2.0 ** -14 * np.sqrt(r)
-    eR = np.linalg.norm(R - (-2 * R).astype(np.float16).astype(np.float64) / -2, axis=1) + flush
-    with np.errstate(over="ignore"):
-        Ck = np.clip(C, -65504, 65504).astype(np.float16).astype(np.float64)
-    ej = np.linalg.norm(C - Ck, axis=1) + flush
-    nR, nC = np.linalg.norm(R, axis=1), np.linalg.norm(C, axis=1)
-    err = np.abs(2 * R @ C.T - 2 * Rq @ Cq.T)
-    delta = 2 * nR[:, None] * ej + 2 * eR[:, None] * (1 + 2.0 ** -8) * nC + ka * nR[:, None] * nC + k2 * nC ** 2
-    assert (err <= delta).all()
+    C[2:6] *= 2.0 ** np.array([[-12], [-20], [-34], [-37]])  # into fp16's subnormals and below
+    R = 2.0 ** (cbexp - 1 + size + rng.uniform(-4, 4, (NT, 1))) * mag[0] * rng.standard_normal((NT, r))
+    R[:8] = C[rng.integers(2, NC, 8)] * 2.0 ** size * rng.uniform(0.9, 1.1, (8, r))
+    C, R = C.astype(f32), R.astype(f32)
+    if grid:
+        C = _f16(np.clip(C, f32(-60000), f32(60000)))
+        up = f32(2.0 ** (9 - size))
+        R = _f16(np.clip(R * up, f32(-60000), f32(60000))) / up
+        R[8:16], R[16:] = C[2:10] * f32(2.0 ** size), -C[10:18] * f32(2.0 ** size)
+    # codebook side (prep_codebook_block)
+    Cq = _f16(np.clip(C, f32(-65504), f32(65504)))
+    n2 = (C * C).sum(1, dtype=f32)
+    eu = (np.sqrt(((C - Cq) ** 2).sum(1, dtype=f32)) * f32(1 + 2.0 ** -15) + f32(tiny)).astype(f32)
+    red = (n2 - n2 * f32(k2s * k2)).astype(f32)
+    hi = _bf(red)
+    mid = _bf(red - hi)
+    lo = _bf(red - hi - mid)
+    cu = (np.sqrt(n2) * f32(1 + 2.0 ** -15)).astype(f32)
+    chi = _bf(cu)
+    rem = cu - chi
+    clo = np.where(rem > 0, _bf_up(np.abs(rem)), _bf_trunc(rem))
+    assert (hi.astype(np.float64) + mid + lo == red).all() and (chi.astype(np.float64) + clo >= cu).all()
+    # token side (rvq_rounds)
+    x = -2 * R
+    mx = np.abs(x).max(1)
+    far = ((mx * tok >= 65504) | (mx < 2.0 ** -3)) & (mx >= 2.0 ** -60) & (mx < 2.0 ** 49)
+    tsc = np.where(far, 2.0 ** (14 - np.floor(np.log2(np.maximum(mx, 2.0 ** -60)))), tok).astype(f32)[:, None]
+    x = x * tsc
+    xq = _f16(x)
+    rn = (f32(0.5) * np.sqrt((x * x).sum(1, dtype=f32)) * f32(1 + 2.0 ** -15) + f32(tiny)).astype(f32)[:, None]
+    en = (f32(0.5) * np.sqrt(((x - xq) ** 2).sum(1, dtype=f32)) * f32(1 + 2.0 ** -15) + f32(tiny)).astype(f32)[:, None]
+    assert np.isfinite(en).all()
+    bco = (2 * en * f32(1.0078125) + f32(ka) * rn).astype(f32)
+    cco = (2 * (rn + en)).astype(f32)
+    b, c = -_bf_up(bco * f32(k1s)), -_bf_up(cco * f32(k1s))
+    delta = (cco * eu + bco * cu + f32(k2) * (tsc * n2)).astype(np.float64) * 1.0002 + 1e-30
+    terms = [tsc * hi, tsc * mid, tsc * lo, b * chi, b * clo, c * _bf_up(eu)]
+    terms += [xq[:, i:i + 1] * Cq[None, :, i] for i in range(r)]
+    exact = tsc.astype(np.float64) * (C.astype(np.float64) ** 2).sum(1) + x.astype(np.float64) @ C.astype(np.float64).T
+    for _ in range(3):
+        L = np.zeros((NT, NC), f32)
+        for i in [0, 1, 2, 3, 4, 5] + list(6 + rng.permutation(r)):
+            L = (L + terms[i]).astype(f32)
+        tagged = ((L.view(np.uint32) & ~np.uint32(15)) | rng.integers(0, 16, L.shape, dtype=np.uint32)).view(f32)
+        for k in (L, tagged):
+            assert (k <= exact + 1e-30).all()
+            assert (exact <= k + (sub + 1) * delta).all()
 
 
 def _encode(x, C):
@@ -148,6 +241,42 @@ def test_tokens_far_above_the_codebook(r, q, part):
     print("mismatched", bad, "exempt", int(exempt.sum()), {k: v[0] for k, v in stats.items() if k.startswith("rvq:")})
     assert bad == 0 and (q < -20 or exempt.mean() < 0.5)
     assert stats["rvq:list_overflows"][0] == 0
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("r", [64, 128, 256])
+@pytest.mark.parametrize("kind", ["outlier", "tokens", "alternate"])
+def test_wide_ranges_are_screened(r, kind):
+    """Sizes over many powers of two, which the screen has to decide without
+    scoring tokens against the whole codebook: one codeword 10^6 times the
+    others, tokens (and the codewords drawn from them) over 2^20, and every
+    second codeword 2^-20 of the others (K = 512: the scale's sample takes one
+    codeword in two)."""
+    K = 512 if kind == "alternate" else 64
+    x = synth.codec_inputs(None, seed=37, **dict(SMALL, T=700, r=r, k=0, L=1, K=K))
+    if kind == "tokens":
+        X = x["X"].copy()
+        e = np.random.default_rng(6).integers(-10, 11, (len(X), 1))
+        x["X"] = np.where((X & 0x7F80) > (11 << 7), X + (e << 7), 0).astype(X.dtype)  # bf16 bits: the exponent
+    C = stress_codebooks(x, 14)
+    C[0, 0] = C[0, 1]  # no zero codeword
+    if kind == "outlier":
+        C[0, 5] *= np.float32(1e6)
+    if kind == "alternate":
+        C[0, ::2] *= np.float32(2.0 ** -20)
+    Z0 = ocodec.project(f64(x, "X"), x["ids"], x["U"], f64(x, "A"), f64(x, "B"), "ambient", "bf16")
+    ref, gap, _ = ocodec.rvq_encode(Z0, C)
+    mapl.profile(2)
+    try:
+        got = _encode(x, C)
+        stats = mapl.profile_report()
+    finally:
+        mapl.profile(0)
+    bad, ex = compare_codes(got, ref, gap)
+    print("mismatched", bad, "exempt", ex, {k: v[0] for k, v in stats.items() if k.startswith("rvq:")})
+    assert bad == 0
+    # a token whose nearest is among the 256 tiny ones may list more than fit
+    assert stats["rvq:list_overflows"][0] <= (3 if kind == "alternate" else 0)
 
 
 @pytest.mark.gpu
