@@ -91,7 +91,9 @@ _SRC_BY_KERNEL = {"gemm_tn": "k_gemm_bf16.hip", "bu_gemm": "k_gemm_bf16.hip", "r
 def kernel_sources(name):
     """Source files whose text decides a chain kernel's code and launch shape."""
     short = name.split(":")[-1]
-    return [_SRC_BY_KERNEL.get(short, "k_prep.hip"), "tn_gemm.hpp", "common.hpp", "kernels.hpp", "mapl_api.cpp"]
+    src = _SRC_BY_KERNEL.get(short, "k_prep.hip")
+    margin = ["rvq_margin.hpp"] if src in ("k_rvq.hip", "k_prep.hip") else []
+    return [src, "tn_gemm.hpp", "common.hpp", "kernels.hpp", "mapl_api.cpp"] + margin
 
 
 def traffic_for(kernel):

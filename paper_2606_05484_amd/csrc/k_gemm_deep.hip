@@ -1,6 +1,5 @@
 // The token-major bf16 product of k_gemm_bf16.hip for launches that its
-// 128-token tiles would spread over a fraction of the chip, and for anchor
-// widths that are not whole 64-column stages:
+// 128-token tiles would spread over a fraction of the chip (any anchor width):
 //
 //   out[t, n] = sum_{c < Ka} A[t, c] W[n, c]  +  sum_{i < Kg} T[ids[t], i] W[n, Ka + i]
 //

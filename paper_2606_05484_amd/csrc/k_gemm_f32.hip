@@ -1,9 +1,10 @@
 // Batched strided fp32 GEMM:
 //   C[b](m,n) = alpha * sum_k A[b](m,k) B[b](k,n) + beta * Cin[b](m,n)
-// (optionally with a second sum whose A rows are gathered by token id) on the fp32 matrix units (v_mfma_f32_32x32x2_f32) or, with GEMM_SPLIT_F16, as
+// (optionally with a second sum whose A rows are gathered by token id) on the
+// fp32 matrix units (v_mfma_f32_32x32x2_f32) or, with GEMM_SPLIT_F16, as
 // products of fp16 pieces on the 16-bit matrix units (k_gemm_x3).  Products
-// with few output tiles, or with strides that the vector loads here do not
-// take, run in k_gemm_f32s.hip.
+// with few output tiles, or with strides or operands of 2 GiB and more that
+// the vector loads here do not take, run in k_gemm_f32s.hip.
 #include "common.hpp"
 #include "kernels.hpp"
 
@@ -520,7 +521,7 @@ __global__ __launch_bounds__(GF_THREADS) __attribute__((amdgpu_waves_per_eu(256 
 
 // The stream-K fix-up: one workgroup per (tile, wave quarter), one wave per
 // 32 x 32 block of the quarter, sums the pieces in piece (= K) order and
-// applies the epilogue of the one-launch kernels (scaling, diagonal); an
+// applies the epilogue of the one-launch kernels (scaling); an
 // off-diagonal tile's mirror is written through a 64 x 64 LDS transpose, in
 // whole rows.
 __global__ __launch_bounds__(256) void k_gemm_sk_fix(GemmF32Args g) {

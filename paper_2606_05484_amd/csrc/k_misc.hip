@@ -155,10 +155,10 @@ __global__ void k_fro_scale(const float* __restrict__ partial, int nblk, int P, 
   }
 }
 
-// nu2 = max_i sum_j |S_ij| per projector, in two launches: blocks of four
-// waves take 16 rows each (a wave 4 rows, every load of the four rows issued
-// before the sums: one round of loads per wave) and write their row maximum;
-// one thread per projector then takes the maximum over its blocks.  r <= 1024.
+// nu2 = max_i sum_j |S_ij| per projector: blocks of four waves take 16 rows
+// each (a wave 4 rows, every load of the four rows issued before the sums: one
+// round of loads per wave) and write their row maximum; the launch that uses
+// nu2 takes the maximum over a projector's blocks.  r <= 1024.
 __global__ __launch_bounds__(256) void k_inf_norm_partial(const float* __restrict__ S, int r,
                                                           float* __restrict__ part) {
   __shared__ float red[4];

@@ -39,7 +39,7 @@
 // from the residuals, a decaying spectrum) the bf16 screen left 34 % of the
 // token-rounds open, every workgroup in pass 2 and some tokens to a rescan of
 // the whole codebook: 420-510 us per call.  With fp16 7 % are open and a
-// sixth of the workgroup-rounds list: 122-128 us.
+// sixth of the workgroup-rounds list: 119-125 us.
 // The fp32 residual stays in registers across rounds, updated as
 // R_{l+1} = R_l - C_l[code_l]; the rescoring reads it from there (through
 // LDS rows), so screening and rescoring see the same R.

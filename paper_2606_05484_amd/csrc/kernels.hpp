@@ -79,7 +79,8 @@ struct GemmF32sArgs {
   const float* pre_a; const float* pre_b;  // per-batch factors of A and B (null: 1)
   int sym_upper;
 };
-// Whether launch_gemm_f32s is the better kernel for an M x N x batch output.
+// Whether launch_gemm_f32s is the better kernel for an M x N x batch output
+// (n-contiguous B; launch_gemm_f32 has a line of its own for the others).
 bool gemm_f32_small(int64_t M, int64_t N, int64_t batch);
 hipError_t launch_gemm_f32s(const GemmF32sArgs& g, hipStream_t s);
 
@@ -213,7 +214,7 @@ PrepJob prep_job_small_gemm(const bf16_t* P, int64_t ldp, const float* Q, int64_
 hipError_t launch_prep_batch(const PrepJob* jobs, int n, hipStream_t s);
 
 // ---------------------------------------------------------------- RVQ (fp16 screen + fp32 rescore)
-// r in {32, 64, 128, 256}.
+// r in {64, 128, 256}.
 struct RvqArgs {
   const float* Z0;     // [T,r] fp32 unquantised coordinates
   const bf16_t* Cb;    // [L,K,r+16] fp16 screening copy with the split norms (rvq_cb_cols)

@@ -1262,7 +1262,7 @@ extern "C" int mapl_anchor_bwd(const mapl_codec_desc* desc, int side, const void
     if ((st = run_id_check(ids, T, D.V, ws, tmp, s))) return st;
   }
   // 1. one launch: dA cleared, the product's second operand, and the tokens
-  //    sorted by id (stable) where one workgroup holds them
+  //    sorted by id (stable) where its bins hold them
   const bool bf = D.x_dtype == MAPL_BF16;
   AnchorPrepArgs pa{};
   pa.dA = dA;
