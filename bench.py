@@ -624,7 +624,7 @@ def main():
         return
     if args.gpus != 1:
         print("bench.py: this build runs on one GPU; --gpus %d is not supported (the codec shards over "
-              "tokens and the SPEL step over projectors, see DESIGN.md)" % args.gpus, file=sys.stderr)
+              "tokens and the SPEL step over projectors)" % args.gpus, file=sys.stderr)
         sys.exit(2)
 
     import torch
