@@ -617,7 +617,7 @@ hipError_t launch_gemm_f32(const GemmF32Args& g, hipStream_t s) {
   // K = 256, 112 tiles 1.15, 128: 1.06, 144: 1.02, 160: 0.90, 256: 0.66; with
   // 64 gathered columns 112: 0.89; N = 64, K = 512, an area of 96: 1.12, 128: 0.96, 192:
   // 1.02, 256: 0.89).
-  const bool few = vm == 3 || g.K2 > 0 ? (int64_t)g.M * g.N < 132ll * (GV_BM * GV_BN) * ((tiles + 255) / 256)
+  const bool few = vm == 3 || g.K2 > 0 ? (int64_t)g.M * g.N * g.batch < 132ll * (GV_BM * GV_BN) * ((tiles + 255) / 256)
                                        : gemm_f32_small(g.M, g.N, g.batch);
   if (vm < 0 || (g.split ? g.sk_part && tiles < 48 : few)) {
     GemmF32sArgs q{};
